@@ -11,20 +11,31 @@
 //      dropped; a block listed twice sets one bit, so it is attended once).  Their union, in
 //      ascending order, is the tile's block list.  The bitmaps and the list are dynamic LDS
 //      sized by the call's last row.
-//   2. The tile walks its block list.  Block j's 16 KiB of K and 16 KiB of V are read from HBM
-//      once per tile (16-byte loads, 1 KiB contiguous per wavefront instruction; every thread
-//      loads four pieces of each) into a double-buffered LDS stage, one block ahead of the math.  K rows keep their 16-byte pieces
-//      XOR-swizzled by the row; V is stored transposed (head dim x token, XOR-swizzled as well) so
-//      that it can be the A operand of P V.  Both swizzles make the operand reads conflict-free
-//      whether LDS serves 16 lanes of a 16-byte read from 64 banks or 32 lanes from 128.
+//   2. The tile walks its block list.  Block j's 16 KiB of K and 16 KiB of V go from HBM straight into
+//      one of two LDS slots (global_load_lds, once per tile), one block ahead of the math; one
+//      barrier per block.  The rows' 16-byte pieces are XOR-swizzled so that every operand read is
+//      conflict-free.  V stays as it lies in memory: P V reads it through the transposing LDS read.
 //   3. A wavefront skips block j for an N-tile none of whose rows lists j.  Otherwise:
 //        S^T = K Q^T on v_mfma_f32_16x16x32_bf16 (M = 16 tokens, N = 16 query-heads, K = 32
 //        dims); query-heads whose row does not list j, and tokens after the row's position, are
 //        masked; online softmax in the exp2 domain;
-//        O^T += V^T P^T on the same MFMA (M = 16 head dims, N = 16 query-heads, K = 32 tokens).
-//      P needs no data movement between the two products: the staged V^T orders each 64-token
-//      block as slots 4 tau + x <-> token tau + 16 x, which is exactly the token order in which
-//      an S^T accumulator lane holds its 16 scores.
+//        O^T += V^T P^T on the same MFMA (M = 16 head dims, N = 16 query-heads, K = 32 tokens), and
+//        the sums of P by two more of them against a tile of ones.
+//      P needs no data movement between the two products: k slot 4 x + i of lane group q is token
+//      16 (2 s + x) + 4 q + i, the order in which an S^T accumulator lane holds its scores.
+//
+// What bounds it: issue.  Per visited N-tile a wavefront issues 34 MFMAs (544 cycles) and about 98
+// VALU instructions, which overlap only in part (a probe: two VALU instructions hide under one
+// 16-cycle MFMA, the third costs 8 cycles), and a block ends with its busiest wavefront (1.28 to
+// 1.5 times the mean).  Reading every block from a 256 KiB footprint instead changes 4 %, so memory is
+// not the limit.  A 32K prefill of 32 / 8 heads, k = 64, neighbouring rows sharing 0.8 of their
+// Forecast variance: 3.83 ms, 535 TFLOP/s of attended pairs (5.89 ms with K and V staged through
+// registers, V transposed on the way, and a branch around every product); the last 8192 rows of 32
+// / 2 heads, k = 96: 1.25 ms (1.97).  Tried and slower: eight wavefronts with a ring of four blocks
+// and one barrier per block (4.70 ms); one wavefront bringing the blocks for 7, 11 or 15 others without
+// barriers (4.0 ms; the ring is too short to even out the wavefronts; 1.12 ms at 16 heads per group);
+// one N-tile per wavefront on 16 wavefronts (4.33 ms).
+//
 // Tiles with the most blocks run first; consecutive workgroups (spread over the XCDs by the
 // dispatcher) take different groups, so each XCD's L2 serves one group's K and V.
 #include <math.h>
@@ -39,11 +50,13 @@ extern __shared__ __align__(16) uint32_t pa_dyn[];
 
 namespace {
 
-constexpr int kPaThreads = 256;            // 4 wavefronts; two workgroups share a CU
-constexpr int kPaQh = 128;                 // query-head rows per tile
-constexpr int kPaKLd = kHeadDim;           // bf16 per staged K row; piece x of row r sits at x ^ (r % 16)
+constexpr int kPaWaves = 4;                // two workgroups share a CU
+constexpr int kPaThreads = 64 * kPaWaves;
+constexpr int kNt = 2;                     // N-tiles of 16 query-heads per wavefront
+constexpr int kPaQh = 16 * kNt * kPaWaves; // query-head rows per tile
 constexpr int kPaMaxBlocks = 4096;         // causal blocks a tile may span
-constexpr int kPaStaticLds = 2 * 2 * kBlock * kHeadDim * 2 + 16;  // the K and V^T double buffers, n_union
+constexpr int kPaSlot = 2 * kBlock * kHeadDim * 2;  // bytes of one slot: a block's K, then its V
+constexpr int kPaStaticLds = 2 * kPaSlot + 16;      // the two slots, n_union
 constexpr int kPaLdsMax = 160 * 1024;      // LDS of one CU
 constexpr float kLog2eP = 1.4426950408889634f;
 
@@ -53,6 +66,28 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   const bf16x2 h = __builtin_convertvector(f32x2{lo, hi}, bf16x2);
   return __builtin_bit_cast(uint32_t, h);
+}
+
+// 16 bytes per lane from global memory (uniform base + the lane's 32-bit offset) straight into LDS:
+// lane l's piece lands at byte address dst + 16 l of the workgroup's LDS (dst wavefront-uniform).
+// Written as one instruction because the builtin makes the compiler wait for every such load in
+// flight before any later LDS read; the instruction has no output register, and the caller waits
+// for it (vmcnt) before the barrier that hands the rows over.
+__device__ __forceinline__ void lds_load16(const void* base, uint32_t off, uint32_t dst) {
+  __asm__ __volatile__("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                       :
+                       : "v"(off), "s"(base), "s"(dst)
+                       : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
+}
+
+// Transposing LDS read: in each 16 lanes, lane 4 r + x addresses 4 consecutive bf16 of row r, columns
+// 4 x .. 4 x + 3; lane i receives column i of rows 0..3.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint2 lds_read_tr16(const char* src) {
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)src));
 }
 
 // Row bitmaps, union bitmap and union list live in dynamic LDS sized by the call (its last row's
@@ -65,16 +100,16 @@ __host__ __device__ inline int pa_dyn_lds_bytes(int rows, int nbt) {
 template <int G>
 __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(AttnArgs a, int n_tiles, int n_groups, int wc) {
   constexpr int TR = kPaQh / G;  // rows per tile
-  constexpr int RN = 16 / G;     // rows per N-tile
+  constexpr int RN = 16 / G;     // rows per N-tile of 16 query-heads; two N-tiles per wavefront
   static_assert(16 % G == 0, "an N-tile holds whole rows");
-  __shared__ __align__(16) uint16_t kst[2][kBlock * kPaKLd];
-  __shared__ __align__(16) uint16_t vst[2][kHeadDim * kBlock];
+  __shared__ __align__(16) uint16_t ring[2 * kPaSlot / 2];
   __shared__ int n_union;
-  uint32_t* rbm = pa_dyn;                                   // [TR][wc] (a tile uses [nrows][W])
+  uint32_t* rbm = pa_dyn;                                   // [TR][wc] (a tile uses [TR][W])
   uint32_t* ubm = pa_dyn + TR * wc;                         // [wc]
   int16_t* ulist = reinterpret_cast<int16_t*>(ubm + wc);    // [wc * 32] >= nbt
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t bm = blockIdx.x % n_groups;
   const int tile = n_tiles - 1 - (int)(blockIdx.x / n_groups);
   const int r0 = tile * TR;
@@ -84,7 +119,7 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(AttnArgs a,
   const int W = (nbt + 31) >> 5;                         // bitmap words per row
 
   // ---- 1. per-row bitmaps and their union
-  for (int i = tid; i < nrows * W; i += kPaThreads) rbm[i] = 0u;
+  for (int i = tid; i < TR * W; i += kPaThreads) rbm[i] = 0u;  // rows past the chunk list nothing
   for (int i = tid; i < W; i += kPaThreads) ubm[i] = 0u;
   __syncthreads();
   {
@@ -123,27 +158,23 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(AttnArgs a,
 
   // ---- per-lane query-head columns: lane (c, q) is column c of both N-tiles, k-chunk q
   const int c = lane & 15, q = lane >> 4;
-  int rl_c[2];
-  bool ok_c[2];
-  int64_t pc[2];
-  bf16x8 qf[2][4];
+  const int rl = wave * kNt * RN + c / G;  // N-tile 0's row within the tile; N-tile 1's is RN rows on
+  bf16x8 qf[kNt][4];
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
-    rl_c[nt] = wave * (32 / G) + nt * RN + c / G;
-    ok_c[nt] = rl_c[nt] < nrows;
-    pc[nt] = p0 + rl_c[nt];
-    const uint16_t* qrow = a.q + ((bm * G + c % G) * a.n_q + r0 + rl_c[nt]) * kHeadDim + 8 * q;
+  for (int nt = 0; nt < kNt; ++nt) {
+    const uint16_t* qrow = a.q + ((bm * G + c % G) * a.n_q + r0 + rl + nt * RN) * kHeadDim + 8 * q;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
-      qf[nt][ks] = as_bf16x8(ok_c[nt] ? ld16(qrow + 32 * ks) : make_uint4(0u, 0u, 0u, 0u));
+      qf[nt][ks] = as_bf16x8(rl + nt * RN < nrows ? ld16(qrow + 32 * ks) : make_uint4(0u, 0u, 0u, 0u));
   }
+  const int pr = (int)(p0 % kBlock) + rl;  // N-tile 0's column position, from the start of the tile's first block
   // z = zscale (q . k): a negative scale is folded into the query's sign bits (exact in bf16), so
   // that the block maximum of z is always zscale times the maximum of q . k.
   float zscale = a.sm_scale * kLog2eP;
   if (zscale < 0.f) {
     zscale = -zscale;
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int nt = 0; nt < kNt; ++nt)
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
         uint4 w = __builtin_bit_cast(uint4, qf[nt][ks]);
@@ -154,220 +185,225 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(AttnArgs a,
         qf[nt][ks] = as_bf16x8(w);
       }
   }
-  // Wait for the query fragments here, once: the loop's own loads are then the only ones in
-  // flight, and the loop's waits can leave the prefetched blocks outstanding.
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
-  f32x4 acc[2][8];
+  // a scale of zero (uniform weights): the smallest positive scale instead, so that masked scores
+  // (-inf) keep weight 0
+  if (zscale == 0.f) zscale = __FLT_MIN__;
+  float m_run[kNt];
+  f32x4 accl[kNt], acc[kNt][8];
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt)
+  for (int nt = 0; nt < kNt; ++nt) {
+    m_run[nt] = -INFINITY;
+    accl[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int md = 0; md < 8; ++md) acc[nt][md] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
 
-  // ---- staging roles.  Every thread copies four 16-byte pieces of K and four of V per block.
-  // K: token u/16, 16-byte part u%16 for u = tid + 256 x.  V: tokens tau + 16 x (x = 0..3), dims
-  // 8 part .. 8 part + 7, with lane l of wavefront w taking tau = 4 w + l % 4, part = l / 4 (each
-  // wavefront load instruction covers 4 whole token rows, 1 KiB contiguous).  One register set
-  // holds the next block's loads while the current block is computed.
-  //
-  // Staged V^T: row d (head dim) holds the block's 64 tokens in slots 4 tau + x <-> token
-  // tau + 16 x, 32 dwords per row; dword w of row d sits at w ^ vsw(d).  An operand read takes
-  // 16 consecutive dims (16 md + c) x 4 k-chunks; vsw's low bits (from dim bits 1..3) give the
-  // dims of one parity distinct dword pairs, so a half wavefront covers 64 banks of 64 and a whole
-  // wavefront 128 of 128.  Its high bits (from dim bits 4, 5, constant over one read) spread the
-  // transposing writes (once per block) to two lanes per bank, the least that 32 lanes of 8-byte
-  // writes into one bank half can take.
-  const int v_tau = 4 * (tid >> 6) + (tid & 3), v_part = (tid & 63) >> 2;
-  const uint16_t* kp = a.k + bm * a.t_cap * kHeadDim + tid * 8;
-  const uint16_t* vp = a.v + bm * a.t_cap * kHeadDim + v_tau * kHeadDim + 8 * v_part;
-  auto vsw = [](int d) { return 2 * ((((d >> 2) & 3) | (((d >> 1) & 1) << 3)) ^ (((d >> 4) & 3) << 2)); };
-  uint4 pre[8];  // K pieces 0..3, V pieces 4..7
-  auto issue = [&](int j) {
-    const int64_t off = (int64_t)j * kBlock * kHeadDim;
-#pragma unroll
-    for (int x = 0; x < 4; ++x) pre[x] = ld16(kp + off + x * 16 * kHeadDim);
-#pragma unroll
-    for (int x = 0; x < 4; ++x) pre[4 + x] = ld16(vp + off + x * 16 * kHeadDim);
-  };
-  auto stage = [&](int buf) {
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const int u = tid + 256 * x;
-      *reinterpret_cast<uint4*>(&kst[buf][(u >> 4) * kPaKLd + (((u & 15) ^ ((u >> 4) & 15)) * 8)]) = pre[x];
-    }
-    const uint32_t* w0 = reinterpret_cast<const uint32_t*>(&pre[4]);
-    const uint32_t* w1 = reinterpret_cast<const uint32_t*>(&pre[5]);
-    const uint32_t* w2 = reinterpret_cast<const uint32_t*>(&pre[6]);
-    const uint32_t* w3 = reinterpret_cast<const uint32_t*>(&pre[7]);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int wi = i >> 1;
-      uint2 d;
-      if (i & 1) {
-        d.x = (w0[wi] >> 16) | (w1[wi] & 0xffff0000u);
-        d.y = (w2[wi] >> 16) | (w3[wi] & 0xffff0000u);
-      } else {
-        d.x = (w0[wi] & 0xffffu) | (w1[wi] << 16);
-        d.y = (w2[wi] & 0xffffu) | (w3[wi] << 16);
-      }
-      const int dim = 8 * v_part + i;
-      *reinterpret_cast<uint2*>(&vst[buf][2 * (dim * 32 + ((2 * v_tau) ^ vsw(dim)))]) = d;
-    }
-  };
-
-  // Online softmax with a lazily raised reference: m_ref[nt] moves only when a block's maximum
-  // exceeds it by more than kHeadroom (log2 units), so most blocks need no rescaling of acc.
-  // P = 2^(z - m_ref) then stays below 2^kHeadroom, well inside bf16 and fp32; the final
+  // Online softmax with a lazily raised reference: P = 2^(z - m_run) keeps its relative precision in
+  // bf16 and fp32 whatever m_run is, so m_run only has to keep P, its sums and the accumulators
+  // inside the exponent range: it is set by a column's first block and moves when a block's maximum
+  // exceeds it by more than kHeadroom (log2 units), which ordinary logits never do again.  The final
   // normalisation by l, accumulated against the same reference, makes the result exact.
-  constexpr float kHeadroom = 8.f;
+  constexpr float kHeadroom = 64.f;
   const int blk0 = (int)(p0 / kBlock);  // blocks >= blk0 may hold tokens after some row's position
 
-  // the four lanes of a column (q = 0..3) exchange through lane ^ 16 and lane ^ 32
-  const int addr32 = (lane ^ 32) << 2;
-  auto xor16 = [](float x) {  // ds_swizzle, bit-mask mode: and 0x1f, xor 0x10 (within 32 lanes)
-    return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), 0x401F));
-  };
-  auto xor32 = [addr32](float x) { return __int_as_float(__builtin_amdgcn_ds_bpermute(addr32, __float_as_int(x))); };
+  // Operand addresses: K row 16 mt + c, piece (4 ks + q) ^ c; V rows 16 mt + 4 q + r (lane's r = c
+  // / 4), dims 16 md + 4 (c % 4) .. + 3, piece (2 md + (c / 2) % 2) ^ 2 (row % 8).  Both swizzles
+  // leave the address of ks or md one XOR away from that of 0; mt is an immediate offset.
+  const int vt = 4 * q + (c >> 2);
+  uint32_t ka0 = (uint32_t)(c * kHeadDim + 8 * (q ^ c)) * 2;
+  uint32_t va0 = (uint32_t)(vt * kHeadDim + 8 * (((c >> 1) & 1) ^ (2 * (vt & 7))) + 4 * (c & 1)) * 2;
 
-  auto compute = [&](int j, int buf) {
-    bool act[2], nt_act[2];
+  // ---- staging: K and V rows go from HBM straight into LDS (16 bytes per lane, one 1 KiB
+  // instruction per 4 token rows, no registers held); instruction u of wavefront w brings rows 16 u +
+  // 4 w .. + 3 of both.  The LDS side of such a load is linear, so the bank swizzle is in which
+  // 16-byte piece of its row a lane asks for: physical piece x of token t holds logical piece
+  // x ^ (t % 16) of K, x ^ 2 (t % 8) of V.
+  const int s_tok = 4 * wave + (lane >> 4);  // token mod 16
+  const uint32_t k_off = (uint32_t)(s_tok * kHeadDim + 8 * ((lane & 15) ^ s_tok)) * 2;
+  const uint32_t v_off = (uint32_t)(s_tok * kHeadDim + 8 * ((lane & 15) ^ (2 * (s_tok & 7)))) * 2;
+  const char* kp = reinterpret_cast<const char*>(a.k + bm * a.t_cap * kHeadDim);
+  const char* vp = reinterpret_cast<const char*>(a.v + bm * a.t_cap * kHeadDim);
+  const uint32_t ring_at = __builtin_amdgcn_readfirstlane(lds_address(ring)) + wave * 1024;
+  auto issue = [&](int j, int slot) {
+    const int64_t off = (int64_t)j * (kBlock * kHeadDim * 2);
+    const uint32_t d = ring_at + slot * kPaSlot;
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      const int rli = ok_c[nt] ? rl_c[nt] : 0;  // never index past the tile's bitmaps
-      act[nt] = ok_c[nt] && ((rbm[rli * W + (j >> 5)] >> (j & 31)) & 1u);
-      nt_act[nt] = __ballot(act[nt]) != 0ull;
-    }
-    if (!(nt_act[0] || nt_act[1])) return;
-    // S^T[token 16 mt + 4 q + i][column c] for both N-tiles
-    f32x4 st[2][4];
-    const uint16_t* kb = &kst[buf][0];
+    for (int u = 0; u < 4; ++u) lds_load16(kp + off + u * 4096, k_off, d + u * 4096);
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      bf16x8 kf[4];
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-        kf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(kb + (16 * mt + c) * kPaKLd + (((4 * ks + q) ^ c) * 8)));
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        st[nt][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (nt_act[nt]) {
-#pragma unroll
-          for (int ks = 0; ks < 4; ++ks) st[nt][mt] = mfma16x16x32(kf[ks], qf[nt][ks], st[nt][mt]);
-        }
-      }
-    }
-    const bool diag = j >= blk0;  // uniform over the workgroup
-    bf16x8 pb[2][2];
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      if (!nt_act[nt]) continue;
-      // maximum over the visible scores: every token, except (in the tile's diagonal blocks)
-      // those after the row's position
-      int lim = kBlock - 1;
-      float e = -INFINITY;
-      if (diag) {
-        const int64_t lim64 = pc[nt] - (int64_t)j * kBlock;
-        lim = (int)(lim64 < kBlock ? lim64 : kBlock - 1);
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (16 * mt + 4 * q + i <= lim) e = fmaxf(e, st[nt][mt][i]);
-      } else {
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-          e = fmaxf(e, fmaxf(fmaxf(st[nt][mt][0], st[nt][mt][1]), fmaxf(st[nt][mt][2], st[nt][mt][3])));
-      }
-      float bmax = act[nt] ? e * zscale : -INFINITY;
-      bmax = fmaxf(bmax, xor16(bmax));
-      bmax = fmaxf(bmax, xor32(bmax));
-      const bool raise = bmax > m_run[nt] + kHeadroom;  // also true on a column's first block
-      if (__ballot(raise) != 0ull) {
-        const float m_new = raise ? bmax : m_run[nt];
-        const float alpha = raise ? __builtin_amdgcn_exp2f(m_run[nt] - m_new) : 1.f;
-        m_run[nt] = m_new;
-        l_run[nt] *= alpha;
-#pragma unroll
-        for (int md = 0; md < 8; ++md) acc[nt][md] *= alpha;
-      }
-      // z - m_ref as one FMA; an inactive column gets -inf, hence P = 0
-      const float off = act[nt] ? -m_run[nt] : -INFINITY;
-      float pz[4][4];
-      float psum = 0.f;
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) pz[mt][i] = __builtin_amdgcn_exp2f(fmaf(st[nt][mt][i], zscale, off));
-      if (diag) {
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (16 * mt + 4 * q + i > lim) pz[mt][i] = 0.f;
-      }
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) psum += pz[mt][i];
-      l_run[nt] += psum;
-      // B operand of k-step s2: slot jj holds token 16 (jj % 4) + 4 q + 2 s2 + jj / 4
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) {
-        uint4 w;
-        w.x = pack_bf16(pz[0][2 * s2], pz[1][2 * s2]);
-        w.y = pack_bf16(pz[2][2 * s2], pz[3][2 * s2]);
-        w.z = pack_bf16(pz[0][2 * s2 + 1], pz[1][2 * s2 + 1]);
-        w.w = pack_bf16(pz[2][2 * s2 + 1], pz[3][2 * s2 + 1]);
-        pb[nt][s2] = as_bf16x8(w);
-      }
-    }
-    // O^T[dim 16 md + 4 q + i][column c] += V^T P^T
-    const uint16_t* vb = &vst[buf][0];
-#pragma unroll
-    for (int md = 0; md < 8; ++md) {
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) {
-        const int dim = 16 * md + c, sw = vsw(dim), dw = 8 * q + 4 * s2;
-        const uint2 v0 = *reinterpret_cast<const uint2*>(vb + 2 * (dim * 32 + (dw ^ sw)));
-        const uint2 v1 = *reinterpret_cast<const uint2*>(vb + 2 * (dim * 32 + ((dw + 2) ^ sw)));
-        const bf16x8 va = as_bf16x8(make_uint4(v0.x, v0.y, v1.x, v1.y));
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-          if (nt_act[nt]) acc[nt][md] = mfma16x16x32(va, pb[nt][s2], acc[nt][md]);
-      }
-    }
+    for (int u = 0; u < 4; ++u) lds_load16(vp + off + u * 4096, v_off, d + kBlock * kHeadDim * 2 + u * 4096);
   };
 
   __syncthreads();  // union list and bitmaps complete
   const int nu = n_union;
-  // Loads and stages run unconditionally (past the list's end they repeat its last block and
-  // fill a buffer nobody reads), so that every path through the loop has the same loads in
-  // flight and the compiler's waits only ever cover the block being staged.
-  auto blk_at = [&](int i) { return (int)ulist[min(i, max(nu - 1, 0))]; };
-  if (nu > 0) {
-    issue(blk_at(0));
-    stage(0);
-  }
-  __syncthreads();
 
-  // Iteration it requests block it + 1, computes block it from buffer it % 2 meanwhile, then
-  // stages block it + 1 into the other buffer.
-  for (int it = 0; it < nu; ++it) {
-    issue(blk_at(it + 1));
-    compute(blk_at(it), it & 1);
-    stage((it + 1) & 1);
-    __syncthreads();
+  // ---- the tile's blocks.  64 entries of the union list at a time: bit i of a row's mask says
+  // whether the row lists entry base + i.  The loop over blocks updates the accumulators in one
+  // place and the raise sits outside it: with both inside, the compiler moves all accumulators
+  // between registers on every block.
+  int it = 0, jv = 0;
+  uint64_t any[kNt] = {}, mine[kNt] = {};
+  auto scan = [&](int base) {
+    const int n = min(64, nu - base);
+    jv = ulist[base + min(lane, n - 1)];
+#pragma unroll
+    for (int nt = 0; nt < kNt; ++nt) any[nt] = 0ull;
+#pragma unroll
+    for (int r = 0; r < kNt * RN; ++r) {
+      const uint64_t b = __ballot(lane < n && ((rbm[(wave * kNt * RN + r) * W + (jv >> 5)] >> (jv & 31)) & 1u));
+      any[r / RN] |= b;
+      if (c / G == r % RN) mine[r / RN] = b;
+    }
+  };
+  if (nu > 0) {
+    scan(0);
+    issue(readlane_i(jv, 0), 0);
+  }
+  bool again = false;  // the block at `it` is resident already: taken up again after a raise
+  for (;;) {
+    bool raise = false;
+    float bmax[kNt];
+#pragma unroll
+    for (int nt = 0; nt < kNt; ++nt) bmax[nt] = -INFINITY;
+    for (; it < nu; ++it) {
+      const int i = it & 63, j = readlane_i(jv, i);
+      bool on[kNt], act[kNt];
+#pragma unroll
+      for (int nt = 0; nt < kNt; ++nt) {
+        on[nt] = ((any[nt] >> i) & 1ull) != 0ull;
+        act[nt] = ((mine[nt] >> i) & 1ull) != 0ull;
+      }
+      if (!again) {
+        // this wavefront's rows of block it have landed and its reads of block it - 1 have returned;
+        // then block it + 1 is requested into the other slot, which every wavefront has left
+        __asm__ __volatile__("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        __asm__ __volatile__("" ::: "memory");
+        if (it + 1 < nu) {
+          const int jn = i == 63 ? __builtin_amdgcn_readfirstlane((int)ulist[it + 1]) : readlane_i(jv, i + 1);
+          issue(jn, (it + 1) & 1);
+        }
+      }
+      again = false;
+      if (!(on[0] || on[kNt - 1])) {
+        if (i == 63 && it + 1 < nu) scan(it + 1);
+        continue;
+      }
+      const char* kb = reinterpret_cast<const char*>(ring) + (it & 1) * kPaSlot;
+      const char* vb = kb + kBlock * kHeadDim * 2;
+      // the XORs are recomputed per block: held across the loop they would spill
+      __asm__ __volatile__("" : "+v"(ka0), "+v"(va0));
+      // S^T[token 16 mt + 4 q + i][column c]
+      bf16x8 kf[4][4];
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+          kf[mt][ks] = as_bf16x8(*reinterpret_cast<const uint4*>(kb + 16 * mt * kHeadDim * 2 + (ka0 ^ (ks << 6))));
+      f32x4 st[kNt][4];
+      bool ask = false;
+#pragma unroll
+      for (int nt = 0; nt < kNt; ++nt) {
+        if (!on[nt]) continue;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+          for (int mt = 0; mt < 4; ++mt)
+            st[nt][mt] = mfma16x16x32(kf[mt][ks], qf[nt][ks], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : st[nt][mt]);
+        if (j >= blk0) {  // a diagonal block: no token after the row's position
+          const int lim = min(pr + nt * RN - (j - blk0) * kBlock, kBlock - 1) - 4 * q;
+#pragma unroll
+          for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (16 * mt + i > lim) st[nt][mt][i] = -INFINITY;
+        }
+        float e = -INFINITY;
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+          e = fmaxf(e, fmaxf(fmaxf(st[nt][mt][0], st[nt][mt][1]), fmaxf(st[nt][mt][2], st[nt][mt][3])));
+        bmax[nt] = act[nt] ? e * zscale : -INFINITY;
+        ask |= bmax[nt] > m_run[nt] + kHeadroom;  // also on a column's first block
+      }
+      if (__ballot(ask) != 0ull) {
+        raise = true;
+        break;
+      }
+      __builtin_amdgcn_s_setprio(1);
+      uint2 vf[4][4];
+      auto read_v = [&](int h) {
+#pragma unroll
+        for (int md = 0; md < 4; ++md)
+#pragma unroll
+          for (int x = 0; x < 4; ++x) vf[md][x] = lds_read_tr16(vb + 16 * x * kHeadDim * 2 + (va0 ^ ((4 * h + md) << 5)));
+      };
+      read_v(0);
+      uint32_t one2 = 0x3f803f80u;  // two bf16 ones
+      __asm__ __volatile__("" : "+v"(one2));
+      const bf16x8 ones = as_bf16x8(make_uint4(one2, one2, one2, one2));
+      bf16x8 pb[kNt][2];
+#pragma unroll
+      for (int nt = 0; nt < kNt; ++nt) {
+        if (!on[nt]) continue;
+        // z - m_run as one FMA; an inactive column gets -inf, hence P = 0
+        const float off = act[nt] ? -m_run[nt] : -INFINITY;
+        float pz[4][4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) pz[mt][i] = __builtin_amdgcn_exp2f(fmaf(st[nt][mt][i], zscale, off));
+        // B operand of k-step s2: slot 4 x + i holds token 16 (2 s2 + x) + 4 q + i
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          uint4 w;
+          w.x = pack_bf16(pz[2 * s2][0], pz[2 * s2][1]);
+          w.y = pack_bf16(pz[2 * s2][2], pz[2 * s2][3]);
+          w.z = pack_bf16(pz[2 * s2 + 1][0], pz[2 * s2 + 1][1]);
+          w.w = pack_bf16(pz[2 * s2 + 1][2], pz[2 * s2 + 1][3]);
+          pb[nt][s2] = as_bf16x8(w);
+          accl[nt] = mfma16x16x32(ones, pb[nt][s2], accl[nt]);  // the column's sum of P in every row
+        }
+      }
+      __builtin_amdgcn_s_setprio(0);
+      // O^T[dim 16 md + 4 q + i][column c] += V^T P^T
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (h == 1) read_v(1);
+#pragma unroll
+        for (int nt = 0; nt < kNt; ++nt) {
+          if (!on[nt]) continue;
+#pragma unroll
+          for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+            for (int md = 0; md < 4; ++md)
+              acc[nt][4 * h + md] = mfma16x16x32(as_bf16x8(make_uint4(vf[md][2 * s2].x, vf[md][2 * s2].y, vf[md][2 * s2 + 1].x, vf[md][2 * s2 + 1].y)),
+                                                 pb[nt][s2], acc[nt][4 * h + md]);
+        }
+      }
+      if (i == 63 && it + 1 < nu) scan(it + 1);
+    }
+    if (!raise) break;
+    again = true;
+#pragma unroll
+    for (int nt = 0; nt < kNt; ++nt) {
+      float m = bmax[nt];
+      m = fmaxf(m, __shfl_xor(m, 16, 64));
+      m = fmaxf(m, __shfl_xor(m, 32, 64));
+      if (!(m > m_run[nt] + kHeadroom)) continue;
+      const float alpha = __builtin_amdgcn_exp2f(m_run[nt] - m);
+      m_run[nt] = m;
+      accl[nt] *= alpha;
+#pragma unroll
+      for (int md = 0; md < 8; ++md) acc[nt][md] *= alpha;
+    }
   }
 
   // ---- normalise and store: lane (c, q) holds dims 16 md + 4 q + i of its column
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
-    float l = l_run[nt];
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
+  for (int nt = 0; nt < kNt; ++nt) {
+    if (rl + nt * RN >= nrows) continue;
+    const float l = accl[nt][0];
     const float inv = l > 0.f ? 1.f / l : 0.f;
-    if (!ok_c[nt]) continue;
-    uint16_t* orow = a.o + ((bm * G + c % G) * a.n_q + r0 + rl_c[nt]) * kHeadDim + 4 * q;
+    uint16_t* orow = a.o + ((bm * G + c % G) * a.n_q + r0 + rl + nt * RN) * kHeadDim + 4 * q;
 #pragma unroll
     for (int md = 0; md < 8; ++md) {
       const f32x4 v = acc[nt][md];

@@ -1,0 +1,76 @@
+"""GPU checks of kernel paths at the sizes where they can go wrong, against the oracle."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2606_04511_amd import inputs
+from paper_2606_04511_amd import sparda as sp
+from parity import abs_bits, compare_attention
+
+pytestmark = pytest.mark.gpu
+SCALE = 1.0 / math.sqrt(128)
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    return torch.device("cuda:0")
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+def shapes(B, H, G, k_total, t_cap, nc_cap, n_init=1, n_local=2, grid=(64, 64)):
+    kw = dict(batch=B, n_kv_heads=H, group_size=G, k_total=k_total, t_cap=t_cap, nc_cap=nc_cap, n_init=n_init,
+              n_local=n_local, cmp_kernel=grid[0], cmp_stride=grid[1])
+    return sp.SpardaShape(**kw), oracle.Shape(**kw)
+
+
+def random_sets(rng, H, n_q, q_pos0, k):
+    """Ascending random sets that hold the row's own block: int16 [1][H][n_q][k], counts."""
+    sel = np.full((1, H, n_q, k), -1, np.int16)
+    cnt = np.zeros((1, H, n_q), np.int16)
+    for m in range(H):
+        for r in range(n_q):
+            blk = (q_pos0 + r) // 64
+            n = min(k, blk + 1)
+            pick = np.append(rng.choice(blk, n - 1, replace=False), blk) if blk else np.zeros(1, np.int64)
+            sel[0, m, r, :n] = np.sort(pick)
+            cnt[0, m, r] = n
+    return sel, cnt
+
+
+# Tile edges (16 to 129 rows of every group size), union lists of 1 to more than 128 entries (the
+# kernel takes 64 at a time), scales of either sign and zero, and a block late in the list whose logits
+# lie more than 64 log2 units above all before it (the softmax reference has to move mid-way).
+@pytest.mark.parametrize("G,n_q,T,k,scale,hot", [
+    (4, 33, 5000, 40, SCALE, 16.0), (4, 64, 64, 1, SCALE, 1.0), (4, 31, 9000, 64, -SCALE, 16.0), (4, 40, 4200, 9, 0.0, 1.0),
+    (16, 17, 8300, 60, SCALE, 16.0), (16, 129, 4160, 3, SCALE, 1.0), (8, 16, 8256, 64, SCALE, 1.0),
+    (2, 65, 4097, 30, SCALE, 16.0), (1, 129, 4100, 20, SCALE, 16.0)])
+def test_attention_tiles(dev, G, n_q, T, k, scale, hot):
+    say(f"attention tiles G{G} n_q{n_q} T{T} k{k} scale {scale:.3f} hot {hot}")
+    H, q_pos0, t_cap = 2, T - n_q, -(-T // 64) * 64
+    rng = np.random.default_rng(100 * G + n_q)
+    s, o = shapes(1, H, G, k, t_cap, t_cap // 64, n_init=0, n_local=1)
+    sel, cnt = random_sets(rng, H, n_q, q_pos0, k)
+    kc = inputs.normal_bf16((1, H, t_cap, 128), 3, 0)
+    v = inputs.normal_bf16((1, H, t_cap, 128), 3, 1)
+    q = inputs.normal_bf16((1, H * G, n_q, 128), 3, 2)
+    j = (q_pos0 // 64) * 3 // 4
+    kc[:, :, 64 * j:64 * j + 64] *= hot
+    ws = torch.empty(16, dtype=torch.uint8, device=dev)
+    out = torch.full((1, H * G, n_q, 128), math.nan, dtype=torch.bfloat16, device=dev)
+    assert sp.sparda_workspace_size(s, sp.SPARDA_OP_SPARSE_ATTN, n_q, q_pos0) == 0
+    sp.sparda_sparse_attn(s, q.to(dev), n_q, q_pos0, kc.to(dev), v.to(dev), 0, torch.from_numpy(sel).to(dev),
+                          torch.from_numpy(cnt).to(dev), scale, out, ws)
+    torch.cuda.synchronize()
+    q16, k16, v16 = inputs.to_u16(q), inputs.to_u16(kc), inputs.to_u16(v)
+    ref = oracle.sparse_attn(o, q16, n_q, q_pos0, k16, v16, 0, sel, cnt, scale)
+    wab = oracle.sparse_attn(o, q16, n_q, q_pos0, k16, abs_bits(v16), 0, sel, cnt, scale)
+    worst = compare_attention(out.float().cpu().numpy(), ref, "tiles", wab)
+    say(f"  max err {worst:.3g} ({compare_attention.last_tight_ratio:.3f} of the tight bar)")
