@@ -16,10 +16,10 @@
 // Kernels:
 //   pair_compress_kernel -- the (2, 1) windows of the raw keys into the workspace: float64 sum of
 //                           the pair, one rounding to bf16 (as every compressed key).
-//   kl_target_kernel     -- for G in {1, 2, 4, 8, 16}: the target's shared weight of every fine
-//                           window for 64 / G rows at a time (64 (row, head) columns on 32x32x16
-//                           MFMA, head_tiles.hpp), into the workspace, so that every fine key
-//                           fragment serves 64 / G rows.
+//   head_stats_kernel, head_weights_kernel (head_tiles.hpp) -- for G in {1, 2, 4, 8, 16}: the
+//                           target's shared weights for 64 / G rows at a time (64 (row, head) columns
+//                           on 32x32x16 MFMA), max-pooled to segments of 16 fine windows in the
+//                           workspace (2 floats per segment instead of one per fine window).
 //   kl_row_kernel        -- one 512-thread workgroup per query row.  Target: the max-pool of those
 //                           weights into the positions, or for other G 16-window x 16-head
 //                           MFMA tiles (A = the windows, B = the group's query rows padded to 16
@@ -70,7 +70,7 @@ struct KlArgs {
   const uint16_t* kp;     // [B][Hkv][nc_cap][D] prediction windows
   float* loss;            // [B][Hkv][n_q]
   float* dF;              // [B][Hkv][n_q][D]
-  float* sw;              // [B][Hkv][n_q][sw_stride] shared target weights per fine window (workspace)
+  float* sw;              // [B][Hkv][n_q][sw_stride] segment maxima of the shared target weights (workspace)
   int64_t sw_stride;
   int32_t lds_pos, lds_top;  // per-position LDS entries (>= 512, a multiple of 16) and top-k list entries
   int64_t nt, nc_cap, q_pos0;
@@ -105,38 +105,8 @@ __device__ __forceinline__ float block_max_f(float x, float* red, int wave, int 
   return m;
 }
 
-// The target's shared weights of many rows on MFMA (G in {1, 2, 4, 8, 16}): a unit is 64 / G rows
-// of one (batch, group) with their heads (head_tiles.hpp), scored against the fine windows
-// complete at the unit's last row; each row stores its weights of the fine windows 0 .. p - 1.
-template <int G>
-__global__ __launch_bounds__(kMtThreads) void kl_target_kernel(KlArgs a, int n_units) {
-  constexpr int U = 64 / G;
-  __shared__ float red_m[kMtWaves][64], red_s[kMtWaves][64];
-  const int n = threadIdx.x & 31;
-  const int n_groups = (int)(gridDim.x / n_units);
-  const int grp = blockIdx.x % n_groups;
-  const int unit = n_units - 1 - (int)(blockIdx.x / n_groups);  // latest rows (most windows) first
-  const int r0 = unit * U;
-  const int nr = min(U, a.n_q - r0);
-  HeadTileRows t;
-  t.n_keys = (int)(a.q_pos0 + r0 + nr - 1);  // fine windows 0 .. p - 1 of the unit's last row
-  t.lo = 0;
-#pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
-    const int c = 32 * nt + n;
-    const int rr = min(c / G, nr - 1);
-    const int64_t p = a.q_pos0 + r0 + rr;
-    t.q[nt] = reinterpret_cast<const uint4*>(a.q) + (((int64_t)grp * G + c % G) * a.n_q + r0 + rr) * kMtRowU4;
-    t.vis[nt] = (int)p - 1;
-    t.hi[nt] = ((n % G) == 0 && c / G < nr) ? (int)p - 1 : -1;
-    t.out[nt] = a.sw + ((int64_t)grp * a.n_q + r0 + rr) * a.sw_stride;
-  }
-  head_tile_shared_weights<G>(t, reinterpret_cast<const uint4*>(a.kt) + (int64_t)grp * a.nt * kMtRowU4,
-                              a.scale_log2, red_m, red_s);
-}
-
-// kPre: the target's shared weights are in a.sw (kl_target_kernel); the row max-pools them into
-// its positions.  Otherwise the row computes them itself (16-window x 16-column MFMA tiles).
+// kPre: the segment maxima of the target's shared weights are in a.sw (head_weights_kernel); the row
+// max-pools them into its positions.  Otherwise the row computes them itself (16-window x 16-column MFMA tiles).
 template <bool kPre>
 __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
   // Per-position arrays, sized by the host for the call's largest row (kl_lds_layout): the pooled
@@ -170,13 +140,13 @@ __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
   // ---- target
   if (kPre) {
     // T_w = the largest shared weight among the fine windows inside position w: tokens [i, i + 2)
-    // within [w s, w s + l), i.e. i in [w s, w s + l - 2]; every position complete at p has them
-    const float* srow = a.sw + row * a.sw_stride;
-    const int gl = a.grid.l, gs = a.grid.s;
+    // within [w s, w s + l), i.e. i in [w s, w s + l - 2]: l / 16 segments of 16 fine windows, the last
+    // one without its last window; every position complete at p has them
+    const float2* seg = reinterpret_cast<const float2*>(a.sw + row * a.sw_stride);
+    const int gs = a.grid.s / 16, gl = a.grid.l / 16;
     for (int w = tid; w < N; w += kDecThreads) {
-      const int i0 = w * gs, i1 = min(w * gs + gl - 2, n_tw - 1);
-      float m = 0.f;
-      for (int i = i0; i <= i1; ++i) m = fmaxf(m, srow[i]);
+      float m = seg[w * gs + gl - 1].x;
+      for (int i = 0; i < gl - 1; ++i) m = fmaxf(m, seg[w * gs + i].y);
       Tp[w] = m;
     }
   } else {  // MFMA tiles of 16 fine windows x the group's heads
@@ -390,16 +360,23 @@ hipError_t launch_indexer_kl(const uint16_t* q, const uint16_t* k, const uint16_
   const size_t lds = (size_t)a.lds_pos * 2 * sizeof(float) + (size_t)a.lds_top * sizeof(int16_t) + (size_t)a.lds_pos;
   const int G = group_size;
   if (G == 1 || G == 2 || G == 4 || G == 8 || G == 16) {  // the target of 64 / G rows per MFMA unit
-    const int n_units = (n_q + 64 / G - 1) / (64 / G);
-    const dim3 grid((unsigned)(rows_g * n_units)), block(kMtThreads);
-    switch (G) {
-      case 1: hipLaunchKernelGGL(kl_target_kernel<1>, grid, block, 0, stream, a, n_units); break;
-      case 2: hipLaunchKernelGGL(kl_target_kernel<2>, grid, block, 0, stream, a, n_units); break;
-      case 4: hipLaunchKernelGGL(kl_target_kernel<4>, grid, block, 0, stream, a, n_units); break;
-      case 8: hipLaunchKernelGGL(kl_target_kernel<8>, grid, block, 0, stream, a, n_units); break;
-      default: hipLaunchKernelGGL(kl_target_kernel<16>, grid, block, 0, stream, a, n_units); break;
-    }
-    hipError_t e = hipGetLastError();
+    HeadTileArgs t = {};
+    t.q = q;
+    t.keys = kt_ws;
+    t.key_cap = a.nt;
+    // the statistics of a row's heads stay in its gradient row (128 floats), which kl_row_kernel
+    // overwrites at the end
+    t.part = dF;
+    t.part_stride = kHeadDim;
+    t.out = sw_ws;
+    t.out_stride = a.sw_stride;
+    t.q_pos0 = q_pos0;
+    t.n_groups = (int32_t)rows_g;
+    t.n_q = n_q;
+    t.grid = WinGrid{2, 1};
+    t.scale_log2 = a.scale_log2;
+    plan_head_tiles(t, G, kHeadDim / (2 * G));
+    hipError_t e = launch_head_tiles<head_tiles::kSegments>(t, G, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kl_row_kernel<true>, dim3((unsigned)(rows_g * n_q)), dim3(kDecThreads), lds, stream, a);
   } else {

@@ -22,10 +22,10 @@
 //    G query rows padded to 16 columns).  Pass 1 keeps an online maximum and sum of 2^z per head,
 //    pass 2 reads the keys again and adds each head's normalised weight into the shared score
 //    of the window, in LDS.
-//  * multi-row tiles (at least 16 rows, G in {1, 2, 4, 8, 16}): mh_tile_kernel scores 64 (row,
-//    head) columns per unit on MFMA in two passes (per-head maximum and sum, then the normalised
-//    weights summed over each row's heads) into the shared scores of the workspace, and
-//    select.hip's row-wise top-k pools and selects.
+//  * multi-row tiles (at least 16 rows, G in {1, 2, 4, 8, 16}): 64 (row, head) columns per unit on
+//    MFMA in two launches (head_tiles.hpp: per-head reference and sum, then the normalised weights
+//    summed over each row's heads) into the shared scores of the workspace, and select.hip's
+//    row-wise top-k pools and selects.
 //  * row-wise (everything else): mh_score_kernel writes every head's score of every complete
 //    window of every row to the workspace, mh_norm_kernel (one workgroup per row) turns them into
 //    the shared scores of the windows that overlap the row's candidates, and the same row-wise
@@ -413,49 +413,6 @@ __global__ __launch_bounds__(256) void mh_norm_kernel(SelectArgs a, int64_t hstr
   }
 }
 
-// ---- multi-row tiles (MFMA, two passes) ------------------------------------------------------
-//
-// Multi-row calls with G in {1, 2, 4, 8, 16}: a unit is U = 64 / G consecutive rows of one
-// (batch, group) with their heads, 64 (row, head) columns (head_tiles.hpp), scored against the
-// windows complete at the unit's last row; each row stores its shared scores of the windows
-// [wf, wl] it selects from, where the row-wise top-k reads them (window wf + x at slot x).
-
-template <int G>
-__global__ __launch_bounds__(kMtThreads) void mh_tile_kernel(SelectArgs a, int n_units, int64_t hstride) {
-  constexpr int U = 64 / G;
-  __shared__ float red_m[kMtWaves][64], red_s[kMtWaves][64];
-  const int lane = threadIdx.x & 63;
-  const int n = lane & 31;
-  const int n_groups = a.batch * a.n_kv_heads;
-  const int grp = blockIdx.x % n_groups;
-  const int unit = n_units - 1 - (int)(blockIdx.x / n_groups);  // latest rows (most windows) first
-  const int r0 = unit * U;
-  const int nr = min(U, a.n_q - r0);
-  const int64_t p_last = a.q_pos0 + r0 + nr - 1;
-  const RowGeom gl = row_geom(p_last, a.n_init, a.n_local, a.k_total);
-  if (gl.n_take >= gl.n_cand) return;  // then every row of the unit takes all its candidates
-  HeadTileRows t;
-  t.n_keys = grid_win_vis(a.grid, p_last) + 1;
-  t.lo = 0;
-#pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
-    const int c = 32 * nt + n;
-    const int rr = min(c / G, nr - 1);
-    const int64_t p = a.q_pos0 + r0 + rr;
-    t.q[nt] = reinterpret_cast<const uint4*>(a.q) + (((int64_t)grp * G + c % G) * a.n_q + r0 + rr) * kMtRowU4;
-    t.vis[nt] = grid_win_vis(a.grid, p);
-    const RowGeom g = row_geom(p, a.n_init, a.n_local, a.k_total);
-    int32_t wf, wl;
-    row_windows(g, a.grid, p, &wf, &wl);
-    t.lo = wf;  // the same for every row
-    const bool own = (n % G) == 0 && c / G < nr && g.n_take < g.n_cand;
-    t.hi[nt] = own ? wl : -1;
-    t.out[nt] = a.ws + ((int64_t)grp * a.n_q + r0 + rr) * a.ws_stride + G * hstride;
-  }
-  head_tile_shared_weights<G>(t, reinterpret_cast<const uint4*>(a.kc) + (int64_t)grp * a.nc_cap * kMtRowU4,
-                              a.scale_log2, red_m, red_s);
-}
-
 // ---- host -----------------------------------------------------------------------------------
 
 enum MhPath { kMhOnePass, kMhTwoPass, kMhRowwise };
@@ -507,16 +464,24 @@ hipError_t launch_multihead_select(const SelectArgs& a, hipStream_t stream) {
     const int nv = grid_win_vis(a.grid, pl) + 1;
     const bool tiles = a.n_q >= kMhTileMinRows && (G == 1 || G == 2 || G == 4 || G == 8 || G == 16);
     if (tiles) {  // many rows: units of 64 (row, head) columns on MFMA, both passes in one kernel
-      const int n_units = (a.n_q + 64 / G - 1) / (64 / G);
-      const dim3 grid((unsigned)((int64_t)n_units * a.batch * a.n_kv_heads)), block(kMtThreads);
-      switch (G) {
-        case 1: hipLaunchKernelGGL(mh_tile_kernel<1>, grid, block, 0, stream, a, n_units, hstride); break;
-        case 2: hipLaunchKernelGGL(mh_tile_kernel<2>, grid, block, 0, stream, a, n_units, hstride); break;
-        case 4: hipLaunchKernelGGL(mh_tile_kernel<4>, grid, block, 0, stream, a, n_units, hstride); break;
-        case 8: hipLaunchKernelGGL(mh_tile_kernel<8>, grid, block, 0, stream, a, n_units, hstride); break;
-        default: hipLaunchKernelGGL(mh_tile_kernel<16>, grid, block, 0, stream, a, n_units, hstride); break;
-      }
-      hipError_t e = hipGetLastError();
+      HeadTileArgs h = {};
+      h.q = a.q;
+      h.keys = a.kc;
+      h.key_cap = a.nc_cap;
+      // a row's statistics in the (here unused) rows of its heads' scores, its weights after them
+      h.part = a.ws;
+      h.part_stride = h.out_stride = a.ws_stride;
+      h.out = a.ws + G * hstride;
+      h.q_pos0 = a.q_pos0;
+      h.n_groups = a.batch * a.n_kv_heads;
+      h.n_q = a.n_q;
+      h.grid = a.grid;
+      h.scale_log2 = a.scale_log2;
+      h.n_init = a.n_init;
+      h.n_local = a.n_local;
+      h.k_total = a.k_total;
+      plan_head_tiles(h, G, hstride / 2);
+      hipError_t e = launch_head_tiles<head_tiles::kWindows>(h, G, stream);
       if (e != hipSuccess) return e;
     } else {
       const int n_chunks = (nv + 255) / 256;

@@ -74,3 +74,43 @@ def test_attention_tiles(dev, G, n_q, T, k, scale, hot):
     wab = oracle.sparse_attn(o, q16, n_q, q_pos0, k16, abs_bits(v16), 0, sel, cnt, scale)
     worst = compare_attention(out.float().cpu().numpy(), ref, "tiles", wab)
     say(f"  max err {worst:.3g} ({compare_attention.last_tight_ratio:.3f} of the tight bar)")
+
+
+# The indexer-training target over chunks of keys: 1, 2 to 3 and 5 or more units of 64 / G rows (the
+# wavefronts of a workgroup share a unit's keys below 4), one and several chunks, and keys late in the
+# context whose logits lie up to 2^100 above the first tile's (the sums are formed again from the
+# true maxima).  With those, a logit z carries an absolute error of up to 128 ulps of sum |q_d k_d|
+# (float32 products and sums), at most 2^-24 * 128 * 170 = 1.3e-3 in log2 units, so weights and losses
+# are off by less than 1e-3 relatively; the others keep float32's 1e-5.
+@pytest.mark.parametrize("G,n_q,T,hot", [(1, 40, 900, 1.0), (1, 130, 2500, 16.0), (2, 90, 1200, 16.0), (4, 16, 700, 16.0),
+                                         (4, 17, 6000, 1.0), (16, 5, 5000, 16.0), (16, 3, 64, 1.0)])
+def test_indexer_kl_target_chunks(dev, G, n_q, T, hot):
+    say(f"indexer target G{G} n_q{n_q} T{T} hot {hot}")
+    H, q_pos0, t_cap, k_top = 2, T - n_q, -(-T // 64) * 64, 8
+    nw = (T - 32) // 16 + 1
+    s, o = shapes(1, H, G, 8, t_cap, nw, grid=(32, 16))
+    k = inputs.normal_bf16((1, H, t_cap, 128), 5, 0)
+    q = inputs.normal_bf16((1, H * G, n_q, 128), 5, 1)
+    f = inputs.normal_bf16((1, H, n_q, 128), 5, 2)
+    k[:, :, T * 3 // 4:T * 3 // 4 + 20] *= hot
+    k16 = inputs.to_u16(k)
+    kcp = oracle.compress_keys(o, k16, T, 0, nw)
+    kct = oracle.compress_keys(oracle.Shape(**{**o.__dict__, "nc_cap": T - 1, "cmp_kernel": 2, "cmp_stride": 1}), k16, T,
+                               0, T - 1)
+    loss = torch.full((1, H, n_q), math.nan, dtype=torch.float32, device=dev)
+    d_f = torch.full((1, H, n_q, 128), math.nan, dtype=torch.float32, device=dev)
+    ws = torch.empty(sp.sparda_workspace_size(s, sp.SPARDA_OP_INDEXER_KL, n_q, q_pos0), dtype=torch.uint8, device=dev)
+    sp.sparda_indexer_kl(s, q.to(dev), k.to(dev), f.to(dev), inputs.from_u16(kcp, dev), n_q, q_pos0, SCALE, k_top, loss,
+                         d_f, ws)
+    torch.cuda.synchronize()
+    rel = 1e-5 if hot == 1.0 else 1e-3
+    worst = 0.0
+    for m in range(H):
+        for r in range(n_q):
+            ref, dref, _, _ = oracle.indexer_kl_row(o, inputs.to_u16(q), kct, 2, 1, inputs.to_u16(f), kcp, n_q, q_pos0,
+                                                    SCALE, k_top, 0, m, r)
+            err, err_d = abs(float(loss[0, m, r]) - ref), np.abs(d_f[0, m, r].cpu().numpy() - dref)
+            assert err <= 4e-6 + rel * abs(ref), f"row {(m, r)}: loss {float(loss[0, m, r])} vs {ref}"
+            assert np.all(err_d <= rel * (np.abs(dref) + np.abs(dref).max()) + 2e-8), f"row {(m, r)}: {err_d.max():.3g}"
+            worst = max(worst, err)
+    say(f"  worst |loss - ref| {worst:.3g}")
