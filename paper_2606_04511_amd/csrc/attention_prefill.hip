@@ -68,21 +68,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, h);
 }
 
-// 16 bytes per lane from global memory (uniform base + the lane's 32-bit offset) straight into LDS:
-// lane l's piece lands at byte address dst + 16 l of the workgroup's LDS (dst wavefront-uniform).
-// Written as one instruction because the builtin makes the compiler wait for every such load in
-// flight before any later LDS read; the instruction has no output register, and the caller waits
-// for it (vmcnt) before the barrier that hands the rows over.
-__device__ __forceinline__ void lds_load16(const void* base, uint32_t off, uint32_t dst) {
-  __asm__ __volatile__("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                       :
-                       : "v"(off), "s"(base), "s"(dst)
-                       : "memory");
-}
-__device__ __forceinline__ uint32_t lds_address(const void* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
-}
-
 // Transposing LDS read: in each 16 lanes, lane 4 r + x addresses 4 consecutive bf16 of row r, columns
 // 4 x .. 4 x + 3; lane i receives column i of rows 0..3.
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -275,7 +260,7 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(AttnArgs a,
       if (!again) {
         // this wavefront's rows of block it have landed and its reads of block it - 1 have returned;
         // then block it + 1 is requested into the other slot, which every wavefront has left
-        __asm__ __volatile__("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        lds_loads_landed();
         __builtin_amdgcn_s_barrier();
         __asm__ __volatile__("" ::: "memory");
         if (it + 1 < nu) {

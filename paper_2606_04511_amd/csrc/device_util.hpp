@@ -204,6 +204,25 @@ __device__ __forceinline__ uint4 ld16_nt(const void* p) {
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
+// 16 bytes per lane from global memory (uniform base + the lane's 32-bit offset) straight into LDS:
+// lane l's piece lands at byte address dst + 16 l of the workgroup's LDS (dst wavefront-uniform).
+// Written as one instruction because the builtin makes the compiler wait for every such load in
+// flight before any later LDS read; the instruction has no output register, and the caller waits
+// for it (vmcnt) before the barrier that hands the rows over.
+__device__ __forceinline__ void lds_load16(const void* base, uint32_t off, uint32_t dst) {
+  __asm__ __volatile__("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                       :
+                       : "v"(off), "s"(base), "s"(dst)
+                       : "memory");
+}
+// Waits for every such load (and every other memory access) of the wavefront.
+__device__ __forceinline__ void lds_loads_landed() {
+  __asm__ __volatile__("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
+}
+
 // z with P(Z > z) = p for a standard normal Z (rational approximation of Abramowitz and Stegun
 // 26.2.23, |error| < 4.5e-4).  Only a first guess for the exact searches that use it.
 __device__ __forceinline__ float upper_normal_quantile(float p) {

@@ -130,17 +130,14 @@ __device__ __forceinline__ void load_rows(const HeadTileArgs& a, const Unit& u, 
 // 32 w + 31, 4 rows per instruction.  Physical 16-byte piece x of row r holds logical piece
 // x ^ (r % 16) ^ (r / 16 % 2): the B operand's reads (32 rows of one piece per lane half) then touch
 // every bank once.
-__device__ __forceinline__ void stage_keys(const uint16_t* keys, int k0, int n_keys, char* slot) {
+__device__ __forceinline__ void stage_keys(const uint16_t* keys, int k0, int n_keys, uint32_t slot) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int r4 = lane >> 4, piece = (lane & 15) ^ (lane >> 4);
   __asm__ __volatile__("" : "+v"(r4), "+v"(piece));  // the eight offsets here: held across the loop they would spill
 #pragma unroll
   for (int i = 0; i < 8; ++i) {  // row 4 i + r4 of the wavefront's 32
     const int key = min(k0 + 32 * wave + 4 * i + r4, n_keys - 1);
-    const uint32_t off = (uint32_t)key * (kHeadDim * 2) + 16 * (piece ^ (4 * (i & 3)) ^ (i >> 2));
-    __builtin_amdgcn_global_load_lds(
-        (const __attribute__((address_space(1))) void*)(reinterpret_cast<const char*>(keys) + off),
-        (__attribute__((address_space(3))) void*)(slot + (32 * wave + 4 * i) * 256), 16, 0, 0);
+    lds_load16(keys, (uint32_t)key * (kHeadDim * 2) + 16 * (piece ^ (4 * (i & 3)) ^ (i >> 2)), slot + (32 * wave + 4 * i) * 256);
   }
 }
 
@@ -189,12 +186,13 @@ template <int G, class F>
 __device__ __forceinline__ void walk(const HeadTileArgs& a, const Unit& u, const bf16x8 (&fa)[2][8], char* slots, F f) {
   const uint16_t* keys = a.keys + (int64_t)u.grp * a.key_cap * kHeadDim;
   const int n_stage = (u.k_hi - u.k_lo + kHtKeys - 1) / kHtKeys;
-  char* now = slots;
-  char* next = slots + kHtSlot;
-  if (n_stage > 0) stage_keys(keys, u.k_lo, u.k_hi, now);
+  const uint32_t slots_at = __builtin_amdgcn_readfirstlane(lds_address(slots));
+  if (n_stage > 0) stage_keys(keys, u.k_lo, u.k_hi, slots_at);
   for (int st = 0; st < n_stage; ++st) {
-    __syncthreads();  // slot `now` has landed (the barrier waits for every load), `next` is free
-    if (st + 1 < n_stage) stage_keys(keys, u.k_lo + (st + 1) * kHtKeys, u.k_hi, next);
+    lds_loads_landed();  // this wavefront's part of the slot is here and its reads of the other returned
+    __syncthreads();
+    const char* now = slots + (st & 1) * kHtSlot;
+    if (st + 1 < n_stage) stage_keys(keys, u.k_lo + (st + 1) * kHtKeys, u.k_hi, slots_at + ((st + 1) & 1) * kHtSlot);
     const int k0 = u.k_lo + st * kHtKeys;
     if (u.live) {
       for (int t = u.share; t < 4 && k0 + 32 * t < u.n_keys; t += u.n_share) {
@@ -205,9 +203,6 @@ __device__ __forceinline__ void walk(const HeadTileArgs& a, const Unit& u, const
         f(key0, c);
       }
     }
-    char* x = now;
-    now = next;
-    next = x;
   }
 }
 

@@ -132,12 +132,12 @@ struct ScoreMaxArgs {
   int32_t n_init, n_local;
 };
 hipError_t launch_score_rowmax(const ScoreMaxArgs& a, hipStream_t stream);
-// Window scores of multi-row calls into the row-wise workspace on MFMA (score_max.hip): units of
-// the rows inside one 64-token block, the windows of each unit's last row.
-hipError_t launch_tile_scores(const SelectArgs& a, hipStream_t stream);
+// Block scores of multi-row calls into the row-wise workspace on MFMA (score_max.hip): a row's first
+// candidate at offset 0, the max-pool over its windows done.  Grids (64, 64) and (32, 16).
+hipError_t launch_block_scores(const SelectArgs& a, hipStream_t stream);
 
-// Row-wise top-k over pooled window scores already in a.ws (row stride a.ws_stride, window wf of
-// the row at offset 0), for the multi-head selector's row-wise path (select.hip).
+// Row-wise top-k over window scores already in a.ws (row stride a.ws_stride, window wf of the row at
+// offset 0), pooled on the way, for the multi-head selector's row-wise path (select.hip).
 hipError_t launch_rowwise_topk(const SelectArgs& a, hipStream_t stream);
 // The InfLLM-V2 multi-head selector (select_multihead.hip).  Workspace floats of a call (0 on the
 // fused decode path); *stride gets the floats per row.

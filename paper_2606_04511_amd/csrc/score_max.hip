@@ -1,5 +1,5 @@
 // score_max.hip -- the Forecast prefill score contraction on 32x32x16 MFMA (Sec. 4.1, Eq. 4):
-// each row's largest candidate score (a measurement of the contraction alone), and the window
+// each row's largest candidate score (a measurement of the contraction alone), and the block
 // scores of the row-wise selection path (at the end of this file).
 //
 // The score contraction on its own: every
@@ -295,72 +295,155 @@ __global__ __launch_bounds__(kSlThreads) void score_rowmax_lds_kernel(ScoreMaxAr
   }
 }
 
-// ---- window scores of many rows, for the row-wise selection path -----------------------------
+// ---- block scores of many rows, for the row-wise selection path ------------------------------
 //
-// Multi-row calls whose rows have more than kSelTileMaxCand candidates keep every window score in
-// the workspace (row stride ws_stride, window wf at slot 0) for the row-wise top-k.  The same
-// units (the rows of one (batch, group) inside one 64-token block) score the windows [wf, wl] of
-// their last row on 32x32x16 MFMA, A = 32 windows of K~ per M-tile (from L2, one M-tile ahead),
-// B = the unit's 64 F rows, so each key fragment serves 64 rows.  Accumulator element e of lane
-// (n, h) is window 8 (e / 4) + 4 h + e % 4 of the M-tile for query column n: each group of four
-// elements is one 16-byte store.  Earlier rows of a unit get up to three windows past their own
-// last visible one; the top-k never reads them.
+// Multi-row calls whose rows have more than kSelTileMaxCand candidates keep every candidate's score in
+// the workspace (row stride ws_stride, the first candidate at slot 0) for the row-wise top-k.  A unit
+// is 64 consecutive rows of one (batch, group), the A operand of two 32-row M-tiles, owned by one
+// wavefront; B = 32 keys, so a row's scores of consecutive candidates lie in consecutive lanes and
+// leave in 128-byte stores.  On the (32, 16) grid lane n of tile u holds window u of block n: the
+// max-pool over a block's five windows (u = -1, the last window of the block before, to 3) is an
+// elementwise maximum over five tiles, and only block scores leave the chip.
+//
+// A workgroup's four wavefronts take four units over one chunk of candidates, staged 128 windows at a
+// time in two LDS slots straight from memory: group n of a slot holds the four rows that lane n reads
+// (windows 4 n .. 4 n + 3 of the stage, or on the one-key-per-block grid keys n, 32 + n, 64 + n, 96 + n),
+// 1040 bytes apart so that the 32 lanes of a read touch every bank once.
+//
+// What bounds it: the matrix cores (five tiles of 16 products per 32 blocks and 64 rows) and the
+// stores.  4096 rows of 8 groups at 128K on the (32, 16) grid: 100-115 us (0.27 GB of block scores, 84
+// GFLOP issued); window scores with keys along the accumulator, read from L2 row by row and stored 16
+// bytes per row, took 386 us and left four times the bytes for the top-k to pool.
+constexpr int kBsGroup = 1040;              // bytes from one group of four staged rows to the next
+constexpr int kBsSlot = 33 * kBsGroup;      // group -1 (the block before the stage's first), then 0 .. 31
+constexpr int kBsUnits = 4;                 // units (wavefronts) per workgroup
 
-__global__ __launch_bounds__(kSmThreads) void tile_score_kernel(SelectArgs a, int blk0, int n_units) {
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n = lane & 31, h = lane >> 5;
+struct BlockScoreArgs {
+  SelectArgs s;
+  int32_t n_wg;                             // workgroups per (batch, group) and chunk
+  int32_t n_chunks, chunk_stages;
+};
+
+template <bool kBlocks>  // one key per block, or the (32, 16) grid
+__global__ __launch_bounds__(64 * kBsUnits, 2) void block_score_kernel(BlockScoreArgs b) {
+  constexpr int kPerStage = kBlocks ? 128 : 32;  // candidates
+  __shared__ __align__(16) char slots[2 * kBsSlot];
+  const SelectArgs& a = b.s;
+  const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n_groups = a.batch * a.n_kv_heads;
-  const int grp = blockIdx.x % n_groups;
-  const int unit = n_units - 1 - (int)(blockIdx.x / n_groups);
-  const int blk = blk0 + unit;
-  const int64_t p_lo = max((int64_t)blk * kBlock, a.q_pos0);
-  const int64_t p_hi = min((int64_t)blk * kBlock + kBlock, a.q_pos0 + a.n_q);
-  const int nr = (int)(p_hi - p_lo);
-  const int64_t row0 = (int64_t)grp * a.n_q + (p_lo - a.q_pos0);
-  const RowGeom g = row_geom(p_hi - 1, a.n_init, a.n_local, a.k_total);
-  if (g.n_take >= g.n_cand) return;  // then every row of the unit takes all its candidates
-  int32_t wf, wl;
-  row_windows(g, a.grid, p_hi - 1, &wf, &wl);
-  const int nwu = wl - wf + 1;
+  const int grp = blockIdx.x % n_groups, x = blockIdx.x / n_groups;
+  const int chunk = x % b.n_chunks, wg = b.n_wg - 1 - x / b.n_chunks;  // latest rows (most candidates) first
+  // the workgroup's last row has the most candidates and sees the most windows
+  const int64_t p_wg = a.q_pos0 + min((wg + 1) * 64 * kBsUnits, a.n_q) - 1;
+  const RowGeom g_wg = row_geom(p_wg, a.n_init, a.n_local, a.k_total);
+  if (g_wg.n_take >= g_wg.n_cand) return;  // then every row takes all its candidates
+  const int c_lo = chunk * b.chunk_stages * kPerStage;
+  const int c_hi = min(c_lo + b.chunk_stages * kPerStage, g_wg.n_cand);
+  if (c_lo >= c_hi) return;
+  int32_t w_min, w_max;  // the windows of its candidates: nothing past them is read
+  row_windows(g_wg, a.grid, p_wg, &w_min, &w_max);
+  // this wavefront's unit
+  const int r0 = (wg * kBsUnits + wave) * 64, nr = min(64, a.n_q - r0);
+  const bool live = nr > 0;
+  const int64_t p0 = a.q_pos0 + r0;
+  const int n_cand = live ? row_geom(p0 + nr - 1, a.n_init, a.n_local, a.k_total).n_cand : 0;
+  const int vis0 = grid_win_vis(a.grid, p0);
 
-  uint4 fb[2][8];
+  bf16x8 fa[2][8];
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
-    const int r = min(32 * nt + n, nr - 1);
-    load_frags(reinterpret_cast<const uint4*>(a.f) + (row0 + r) * kRowU4, h, fb[nt]);
+  for (int mt = 0; mt < 2; ++mt) {
+    const uint16_t* src = a.f + ((int64_t)grp * a.n_q + (live ? r0 + min(32 * mt + n, nr - 1) : 0)) * kHeadDim + 32 * h;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) fa[mt][s] = as_bf16x8(ld16(src + 64 * (s >> 2) + 8 * (s & 3)));
   }
-  const uint4* kc = reinterpret_cast<const uint4*>(a.kc) + ((int64_t)grp * a.nc_cap + wf) * kRowU4;
-  const int n_mt = (nwu + 31) / 32;
-  float* out0 = a.ws + (row0 + n) * a.ws_stride;
-  float* out1 = a.ws + (row0 + 32 + n) * a.ws_stride;
-  auto store = [&](int mt, const f32x16& c0, const f32x16& c1) {
+  const uint16_t* keys = a.kc + (int64_t)grp * a.nc_cap * kHeadDim;
+  const uint32_t slots_at = __builtin_amdgcn_readfirstlane(lds_address(slots));
+  const int r4 = lane >> 4;
+  // window of row r4 of group i in the stage whose first candidate is c0
+  auto stage = [&](int c0, uint32_t slot) {
+    auto bring = [&](int i) {
+      const int w = kBlocks ? g_wg.cand_lo + c0 + 32 * r4 + i : 4 * (g_wg.cand_lo + c0 + i) + r4;
+      const int key = min(max(w, 0), w_max);
+      lds_load16(keys, (uint32_t)key * (kHeadDim * 2) + 16 * (lane & 15), slot + (i + 1) * kBsGroup);
+    };
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int x = 32 * mt + 8 * q + 4 * h;
-      if (x < nwu) {
-        if (n < nr) *reinterpret_cast<float4*>(out0 + x) = make_float4(c0[4 * q], c0[4 * q + 1], c0[4 * q + 2], c0[4 * q + 3]);
-        if (32 + n < nr)
-          *reinterpret_cast<float4*>(out1 + x) = make_float4(c1[4 * q], c1[4 * q + 1], c1[4 * q + 2], c1[4 * q + 3]);
-      }
-    }
+    for (int i = 0; i < 8; ++i) bring(8 * wave + i);
+    if (!kBlocks && wave == 0) bring(-1);
   };
-  if (w < n_mt) {
-    uint4 ab[2][8];
-    auto arow = [&](int mt) { return kc + (int64_t)min(32 * min(mt, n_mt - 1) + n, nwu - 1) * kRowU4; };
-    load_frags(arow(w), h, ab[0]);
-    for (int mt = w; mt < n_mt; mt += 2 * kSmWaves) {
-      load_frags(arow(mt + kSmWaves), h, ab[1]);
-      __builtin_amdgcn_sched_barrier(0);  // keep the request ahead of the products
-      f32x16 c0, c1;
-      mma_tile(ab[0], fb, c0, c1);
-      store(mt, c0, c1);
-      load_frags(arow(mt + 2 * kSmWaves), h, ab[0]);
-      __builtin_amdgcn_sched_barrier(0);
-      if (mt + kSmWaves < n_mt) {
-        mma_tile(ab[1], fb, c0, c1);
-        store(mt + kSmWaves, c0, c1);
+  const int n_stage = (c_hi - c_lo + kPerStage - 1) / kPerStage;
+  stage(c_lo, slots_at);
+  float* const out = a.ws + ((int64_t)grp * a.n_q + r0) * a.ws_stride;
+  for (int st = 0; st < n_stage; ++st) {
+    lds_loads_landed();  // this wavefront's part of the slot is here and its reads of the other returned
+    __syncthreads();
+    const char* now = slots + (st & 1) * kBsSlot;
+    const int c0 = c_lo + st * kPerStage;
+    if (st + 1 < n_stage) stage(c0 + kPerStage, slots_at + ((st + 1) & 1) * kBsSlot);
+    if (!live || c0 >= n_cand) continue;
+    auto tile = [&](int group, int row, f32x16& c0_, f32x16& c1_) {
+      const char* src = now + (n + 1 + group) * kBsGroup + row * 256 + 64 * h;
+      bf16x8 k[8];
+#pragma unroll
+      for (int s = 0; s < 8; ++s) k[s] = as_bf16x8(*reinterpret_cast<const uint4*>(src + 128 * (s >> 2) + 16 * (s & 3)));
+#pragma unroll
+      for (int e = 0; e < 16; ++e) c0_[e] = c1_[e] = 0.f;
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        c0_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0][s], k[s], c0_, 0, 0, 0);
+        c1_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1][s], k[s], c1_, 0, 0, 0);
       }
+    };
+    // accumulator element e of lane (n, h) is row 8 (e / 4) + 4 h + e % 4 of the M-tile, key n
+    auto store = [&](int c, const f32x16& s0, const f32x16& s1) {
+      if (c + n >= n_cand) return;
+      int64_t stride = a.ws_stride;
+      __asm__ __volatile__("" : "+s"(stride));  // row addresses here: held across the loop they would spill
+      float* d = out + (int64_t)(4 * h) * stride + c + n;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int r = 8 * (e >> 2) + (e & 3);
+        if (r + 4 * h < nr) d[r * stride] = s0[e];
+        if (32 + r + 4 * h < nr) d[(32 + r) * stride] = s1[e];
+      }
+    };
+    if (kBlocks) {
+#pragma unroll 1
+      for (int t = 0; t < 4 && c0 + 32 * t < n_cand; ++t) {
+        f32x16 s0, s1;
+        tile(0, t, s0, s1);
+        store(c0 + 32 * t, s0, s1);
+      }
+    } else {
+      const int blk = g_wg.cand_lo + c0 + n;  // the lane's block
+      f32x16 s0, s1;
+      tile(-1, 3, s0, s1);
+      if (blk == 0) {  // no window before block 0
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s0[e] = s1[e] = -INFINITY;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        f32x16 t0, t1;
+        tile(0, u, t0, t1);
+        if (4 * (g_wg.cand_lo + c0 + 31) + u > vis0) {  // windows that some row does not see whole
+          // the last token of the lane's window, from the position of the lane half's first row
+          int tail = 16 * (4 * blk + u) + 31 - (int)p0 - 4 * h;
+          __asm__ __volatile__("" : "+v"(tail));  // the comparisons here: held across the loop they would spill
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int r = 8 * (e >> 2) + (e & 3);
+            if (tail > r) t0[e] = -INFINITY;
+            if (tail > 32 + r) t1[e] = -INFINITY;
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          s0[e] = fmaxf(s0[e], t0[e]);
+          s1[e] = fmaxf(s1[e], t1[e]);
+        }
+      }
+      store(c0, s0, s1);
     }
   }
 }
@@ -384,11 +467,24 @@ hipError_t launch_score_rowmax(const ScoreMaxArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_tile_scores(const SelectArgs& a, hipStream_t stream) {
-  const int blk0 = (int)(a.q_pos0 / kBlock);
-  const int n_units = (int)((a.q_pos0 + a.n_q - 1) / kBlock) - blk0 + 1;
-  const int64_t wgs = (int64_t)n_units * a.batch * a.n_kv_heads;
-  hipLaunchKernelGGL(tile_score_kernel, dim3((unsigned)wgs), dim3(kSmThreads), 0, stream, a, blk0, n_units);
+hipError_t launch_block_scores(const SelectArgs& a, hipStream_t stream) {
+  BlockScoreArgs b;
+  b.s = a;
+  const int n_groups = a.batch * a.n_kv_heads;
+  const bool blocks = grid_is_blocks(a.grid);
+  const RowGeom g = row_geom(a.q_pos0 + a.n_q - 1, a.n_init, a.n_local, a.k_total);
+  const int stages = (g.n_cand + (blocks ? 127 : 31)) / (blocks ? 128 : 32);
+  b.n_wg = (a.n_q + 64 * kBsUnits - 1) / (64 * kBsUnits);
+  // chunks of candidates so that about four workgroups per CU are in flight, at least four stages each
+  int64_t chunks = (1024 + (int64_t)n_groups * b.n_wg - 1) / ((int64_t)n_groups * b.n_wg);
+  chunks = std::max<int64_t>(1, std::min<int64_t>(chunks, (stages + 3) / 4));
+  b.chunk_stages = (int)((stages + chunks - 1) / chunks);
+  b.n_chunks = (stages + b.chunk_stages - 1) / b.chunk_stages;
+  const dim3 grid((unsigned)((int64_t)n_groups * b.n_wg * b.n_chunks)), block(64 * kBsUnits);
+  if (blocks)
+    hipLaunchKernelGGL(block_score_kernel<true>, grid, block, 0, stream, b);
+  else
+    hipLaunchKernelGGL(block_score_kernel<false>, grid, block, 0, stream, b);
   return hipGetLastError();
 }
 

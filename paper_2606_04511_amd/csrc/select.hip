@@ -10,9 +10,10 @@
 //
 // Two paths:
 //  * row-wise (decode, n_q == 1, and long multi-row cases): a bandwidth-bound GEMV kernel writes
-//    the candidate scores of each row to a float32 scratch row; a second kernel runs one
-//    wavefront per row that finds the exact k-th key by an 8-bit-digit radix select over a
-//    wave-private LDS histogram and emits the chosen indices in ascending order with ballots.
+//    the candidate scores of each row to a float32 scratch row (from 16 rows on, MFMA units write
+//    pooled block scores, score_max.hip); a second kernel runs one wavefront per row that finds the
+//    exact k-th key by counts over keys in registers (up to 4096 candidates) or an 8-bit-digit radix
+//    select over a wave-private LDS histogram, and emits the chosen indices in ascending order.
 //  * fused decode (one row per (batch, group), <= 16384 candidates): one workgroup per row keeps
 //    the row's scores in LDS and runs the block-wide top-k there (select_block.hpp).
 //  * fused tile (multi-row prefill with <= 512 candidates per 64-row tile): select_prefill.hip.
@@ -70,39 +71,210 @@ __global__ __launch_bounds__(256) void rowwise_score_kernel(SelectArgs a, int n_
 }
 
 
-// Rows with at most this many candidates keep their pooled block keys in LDS for the radix passes
-// (8 KiB per wavefront); longer rows pool from the workspace on every pass.
-constexpr int kRowTopkLdsKeys = 2048;
+// Rows with at most this many candidates keep their block keys in registers (row_topk_kernel); longer
+// rows run the radix passes over the workspace (rowwise_topk_kernel).
+constexpr int kRowTopkMax = 4096;
+
+// kPooled: the row's block scores are in the workspace, candidate 0 at slot 0 (block_score_kernel);
+// otherwise its window scores, window wf at slot 0.
+template <bool kPooled>
+__device__ __forceinline__ float candidate_score(const SelectArgs& a, const float* sc, int cand_lo, int i, int32_t wf,
+                                                 int32_t wvis) {
+  return kPooled ? sc[i] : pooled_score(sc, a.grid, cand_lo + i, wf, wvis);
+}
 
 // One wavefront per row: forced blocks, padding, count, and the radix top-k over the scratch row.
+template <bool kPooled>
 __global__ __launch_bounds__(256) void rowwise_topk_kernel(SelectArgs a, int64_t n_rows) {
   __shared__ __align__(16) uint32_t hist[4][256];
-  __shared__ uint32_t keys[4][kRowTopkLdsKeys];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + wave;
   if (row >= n_rows) return;
-  const int r = (int)(row % a.n_q);
-  const RowGeom g = row_geom(a.q_pos0 + r, a.n_init, a.n_local, a.k_total);
+  const int64_t p = a.q_pos0 + (int)(row % a.n_q);
+  const RowGeom g = row_geom(p, a.n_init, a.n_local, a.k_total);
   int16_t* out = a.sel + row * a.k_total;
   emit_forced(out, g, a.k_total, lane);
   if (lane == 0) a.cnt[row] = (int16_t)(g.n_forced + g.n_take);
   const float* sc = a.ws + row * a.ws_stride;
-  const int64_t p = a.q_pos0 + r;
   int32_t wf, wl;
   row_windows(g, a.grid, p, &wf, &wl);
   const int32_t wvis = grid_win_vis(a.grid, p);
-  const WinGrid grid = a.grid;
-  if (g.n_take < g.n_cand && g.n_cand <= kRowTopkLdsKeys) {
-    // pool once: the passes and the emission then read LDS instead of the workspace
-    uint32_t* kw = keys[wave];
-#pragma unroll 4
-    for (int i = lane; i < g.n_cand; i += kWave) kw[i] = score_key(pooled_score(sc, grid, g.cand_lo + i, wf, wvis));
-    wave_lds_sync();
-    wave_topk_emit([&](int i) { return kw[i]; }, g.n_cand, g.n_take, g.cand_lo, hist[wave], out + g.init_hi);
+  wave_topk_emit([&](int i) { return score_key(candidate_score<kPooled>(a, sc, g.cand_lo, i, wf, wvis)); }, g.n_cand,
+                 g.n_take, g.cand_lo, hist[wave], out + g.init_hi);
+}
+
+// The same for rows of at most 64 R candidates, their keys (order-preserving score bits) in registers:
+// candidate 64 i + lane is key i of the lane.  The n-th largest key is bracketed by counts (a compare
+// and a scalar bit count per 64 candidates): two thresholds around a normal-model guess first, then
+// one at a time by linear interpolation, every third by bisection, until at most 64 keys are left
+// between them; those are compacted into LDS, one per lane, and ranked.  The emission walks the
+// registers in index order; keys equal to the n-th go to the lowest indices.
+//
+// What bounds it: VALU issue, about 1000 instructions per row of 2048.  32 768 rows of 2045 block
+// scores: 120-140 us; pooling window scores into LDS and four radix passes there took 730 us.
+template <int R, bool kPooled>
+__global__ __launch_bounds__(256) void row_topk_kernel(SelectArgs a, int64_t n_rows) {
+  __shared__ uint32_t list[4][64];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t row = (int64_t)blockIdx.x * 4 + wave;
+  if (row >= n_rows) return;
+  const int64_t p = a.q_pos0 + (int)(row % a.n_q);
+  const RowGeom g = row_geom(p, a.n_init, a.n_local, a.k_total);
+  int16_t* out = a.sel + row * a.k_total;
+  emit_forced(out, g, a.k_total, lane);
+  if (lane == 0) a.cnt[row] = (int16_t)(g.n_forced + g.n_take);
+  out += g.init_hi;
+  const int C = g.n_cand, n = g.n_take;
+  if (n >= C) {
+    for (int i = lane; i < C; i += kWave) out[i] = (int16_t)(g.cand_lo + i);
     return;
   }
-  wave_topk_emit([&](int i) { return score_key(pooled_score(sc, grid, g.cand_lo + i, wf, wvis)); }, g.n_cand,
-                 g.n_take, g.cand_lo, hist[wave], out + g.init_hi);
+  if (n <= 0) return;
+  const float* sc = a.ws + row * a.ws_stride;
+  int32_t wf, wl;
+  row_windows(g, a.grid, p, &wf, &wl);
+  const int32_t wvis = grid_win_vis(a.grid, p);
+  uint32_t key[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {  // slots past the row's candidates: key 0, below every score
+    const int c = 64 * i + lane;
+    const float x = candidate_score<kPooled>(a, sc, g.cand_lo, min(c, C - 1), wf, wvis);
+    key[i] = c < C ? score_key(x) : 0u;
+  }
+  uint32_t k_max = 0u, k_min = ~0u;
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    k_max = max(k_max, key[i]);
+    k_min = min(k_min, 64 * i + lane < C ? key[i] : ~0u);
+  }
+  k_max = row16_max(k_max);
+  k_min = row16_min(k_min);
+  k_max = max(k_max, (uint32_t)__shfl_xor((int)k_max, 16, kWave));
+  k_min = min(k_min, (uint32_t)__shfl_xor((int)k_min, 16, kWave));
+  k_max = __builtin_amdgcn_readfirstlane(max(k_max, (uint32_t)__shfl_xor((int)k_max, 32, kWave)));
+  k_min = __builtin_amdgcn_readfirstlane(min(k_min, (uint32_t)__shfl_xor((int)k_min, 32, kWave)));
+  auto above = [&](uint32_t t) {  // keys larger than t
+    int m = 0;
+#pragma unroll
+    for (int i = 0; i < R; ++i) m += (int)__popcll(__ballot(key[i] > t));
+    return m;
+  };
+  // count(> lo) = c_lo >= n, count(> hi) = c_hi < n throughout
+  uint32_t lo = k_min > 0u ? k_min - 1u : 0u, hi = k_max;
+  int c_lo = C, c_hi = 0;
+  auto cut = [&](uint32_t t) {
+    if (t <= lo || t >= hi) return;
+    const int m = above(t);
+    if (m >= n) {
+      lo = t;
+      c_lo = m;
+    } else {
+      hi = t;
+      c_hi = m;
+    }
+  };
+  {
+    // Mean and deviation of the scores (window weights are all positive and skewed: of their keys,
+    // which grow with the logarithm), and thresholds about 20 keys to either side of the guess.
+    float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const float x = kPooled ? key_value(key[i]) : (float)(key[i] - k_min);
+      if (64 * i + lane < C) {
+        s1 += x;
+        s2 = fmaf(x, x, s2);
+      }
+    }
+    s1 = row16_sum(s1);
+    s2 = row16_sum(s2);
+    s1 += __shfl_xor(s1, 16, kWave);
+    s2 += __shfl_xor(s2, 16, kWave);
+    s1 = readlane_f(s1 + __shfl_xor(s1, 32, kWave), 0);
+    s2 = readlane_f(s2 + __shfl_xor(s2, 32, kWave), 0);
+    const float mean = s1 / C, dev = __builtin_amdgcn_sqrtf(fmaxf(s2 / C - mean * mean, 0.f));
+    const float z = upper_normal_quantile((float)n / C);
+    const float step = 20.f * dev / (C * 0.3989f * __builtin_amdgcn_exp2f(-0.7213f * z * z));
+    auto key_at = [&](float x) {
+      if (kPooled) return score_key(x);
+      return x > 0.f && x < 4e9f ? k_min + (uint32_t)x : 0u;
+    };
+    const float t0 = mean + z * dev;
+    if (t0 - t0 == 0.f && step - step == 0.f) {  // finite
+      cut(__builtin_amdgcn_readfirstlane(key_at(t0 - step)));
+      cut(__builtin_amdgcn_readfirstlane(key_at(t0 + step)));
+    }
+  }
+  for (int pass = 0;; ++pass) {  // every cut narrows (lo, hi)
+    if (c_lo - c_hi <= 64 || hi - lo <= 1u || c_lo == n) break;
+    const uint32_t span = hi - lo;
+    uint32_t t = lo + span / 2;
+    if (pass % 3 != 2) {
+      const float f = ((float)(c_lo - n) + 0.5f) / (float)(c_lo - c_hi);  // in (0, 1)
+      t = lo + min(max((uint32_t)(f * (float)span), 1u), span - 1u);
+    }
+    cut(t);
+  }
+  // T: keys above it are chosen, and the first `equal` keys equal to it
+  uint32_t T = lo;
+  int equal = 0;
+  if (c_lo != n) {
+    if (c_lo - c_hi <= 64) {  // rank the keys in (lo, hi]
+      int base = 0;
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const bool in = key[i] > lo && key[i] <= hi;
+        const uint64_t b = __ballot(in);
+        if (b != 0ull) {
+          if (in) list[wave][base + mbcnt64(b)] = key[i];
+          base += (int)__popcll(b);
+        }
+      }
+      wave_lds_sync();
+      const uint32_t mine = lane < base ? list[wave][lane] : 0u;
+      int more = 0, same = 0;
+      for (int j = 0; j < base; ++j) {
+        const uint32_t o = (uint32_t)readlane_i((int)mine, j);
+        more += o > mine;
+        same += o == mine;
+      }
+      const int want = n - c_hi - 1;  // the n-th largest key's rank in the list
+      const uint64_t hit = __ballot(lane < base && more <= want && want < more + same);
+      const int src = hit ? (int)__builtin_ctzll(hit) : 0;  // some lane holds it
+      T = (uint32_t)readlane_i((int)mine, src);
+      equal = n - c_hi - readlane_i(more, src);
+    } else {  // hi - lo == 1: more than 64 keys equal to hi
+      T = hi;
+      equal = n - c_hi;
+    }
+  }
+  int base = 0, ties = 0;
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const uint64_t eq = equal > ties ? __ballot(key[i] == T) : 0ull;
+    const uint64_t gt = __ballot(key[i] > T);
+    if ((eq | gt) == 0ull) continue;
+    const bool chosen = key[i] > T || (((eq >> lane) & 1ull) && ties + mbcnt64(eq) < equal);
+    const uint64_t b = __ballot(chosen);
+    if (chosen) out[base + mbcnt64(b)] = (int16_t)(g.cand_lo + 64 * i + lane);
+    base += (int)__popcll(b);
+    ties += (int)__popcll(eq);
+  }
+}
+
+template <bool kPooled>
+static hipError_t launch_topk(const SelectArgs& a, hipStream_t stream) {
+  const int64_t rows = (int64_t)a.batch * a.n_kv_heads * a.n_q;
+  const int C = row_geom(a.q_pos0 + a.n_q - 1, a.n_init, a.n_local, a.k_total).n_cand;  // the last row has the most
+  const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
+  if (C <= 1024)
+    hipLaunchKernelGGL((row_topk_kernel<16, kPooled>), grid, block, 0, stream, a, rows);
+  else if (C <= 2048)
+    hipLaunchKernelGGL((row_topk_kernel<32, kPooled>), grid, block, 0, stream, a, rows);
+  else if (C <= kRowTopkMax)
+    hipLaunchKernelGGL((row_topk_kernel<64, kPooled>), grid, block, 0, stream, a, rows);
+  else
+    hipLaunchKernelGGL(rowwise_topk_kernel<kPooled>, grid, block, 0, stream, a, rows);
+  return hipGetLastError();
 }
 
 // ---- fused decode path ---------------------------------------------------------------------
@@ -142,6 +314,8 @@ constexpr int64_t kDecodeSplitRows = 256;
 // Multi-row calls on the row-wise path with at least this many rows score on MFMA.
 constexpr int32_t kTileScoreMinRows = 16;
 
+static bool tile_grid(WinGrid grid) { return grid_is_blocks(grid) || (grid.l == 32 && grid.s == 16); }
+
 static SelectPath select_path(int64_t rows, int32_t n_q, int64_t q_pos0, int32_t n_init, int32_t n_local,
                               WinGrid grid) {
   const int64_t p = q_pos0 + n_q - 1;
@@ -155,8 +329,7 @@ static SelectPath select_path(int64_t rows, int32_t n_q, int64_t q_pos0, int32_t
     return rows < kDecodeSplitRows && nw >= 1024 ? kPathDecodeSplit : kPathDecode;
   }
   // multi-row: the fused tile kernel serves both grids up to kSelTileMaxCand candidates per row
-  const bool tile_grid = grid_is_blocks(grid) || (grid.l == 32 && grid.s == 16);
-  return tile_grid && g.n_cand <= kSelTileMaxCand ? kPathTile : kPathRowwise;
+  return tile_grid(grid) && g.n_cand <= kSelTileMaxCand ? kPathTile : kPathRowwise;
 }
 
 int select_decode_path(int64_t rows, int32_t n_q, int64_t q_pos0, int32_t n_init, int32_t n_local, WinGrid grid) {
@@ -180,11 +353,7 @@ bool select_needs_scratch(int64_t rows, int32_t n_q, int64_t q_pos0, int32_t n_i
   return path == kPathRowwise || path == kPathDecodeSplit;
 }
 
-hipError_t launch_rowwise_topk(const SelectArgs& a, hipStream_t stream) {
-  const int64_t rows = (int64_t)a.batch * a.n_kv_heads * a.n_q;
-  hipLaunchKernelGGL(rowwise_topk_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, a, rows);
-  return hipGetLastError();
-}
+hipError_t launch_rowwise_topk(const SelectArgs& a, hipStream_t stream) { return launch_topk<false>(a, stream); }
 
 hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
   const int64_t rows = (int64_t)a.batch * a.n_kv_heads * a.n_q;
@@ -198,20 +367,18 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
   const RowGeom gl = row_geom(pl, a.n_init, a.n_local, a.k_total);
   int32_t wf, wl;
   row_windows(gl, a.grid, pl, &wf, &wl);
-  if (gl.n_cand > 0 && wl >= wf && a.n_q >= kTileScoreMinRows) {
+  if (gl.n_cand > 0 && wl >= wf && a.n_q >= kTileScoreMinRows && tile_grid(a.grid)) {
     // many rows: 64-row units score on MFMA, each key fragment shared by the unit's rows
-    hipError_t e = launch_tile_scores(a, stream);
-    if (e != hipSuccess) return e;
+    hipError_t e = launch_block_scores(a, stream);
+    return e != hipSuccess ? e : launch_topk<true>(a, stream);
   } else if (gl.n_cand > 0 && wl >= wf) {  // the last row scores the most windows
     const int n_chunks = (wl - wf + 1 + 255) / 256;
     hipLaunchKernelGGL(rowwise_score_kernel, dim3((unsigned)(rows * n_chunks)), dim3(256), 0, stream, a, n_chunks);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (path == kPathDecodeSplit)
-    hipLaunchKernelGGL(decode_topk_kernel, dim3((unsigned)rows), dim3(kDecThreads), 0, stream, a);
-  else
-    hipLaunchKernelGGL(rowwise_topk_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, a, rows);
+  if (path != kPathDecodeSplit) return launch_topk<false>(a, stream);
+  hipLaunchKernelGGL(decode_topk_kernel, dim3((unsigned)rows), dim3(kDecThreads), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2606_04511_amd import inputs
 from paper_2606_04511_amd import sparda as sp
-from parity import abs_bits, compare_attention
+from parity import abs_bits, compare_attention, compare_selection
 
 pytestmark = pytest.mark.gpu
 SCALE = 1.0 / math.sqrt(128)
@@ -114,3 +114,40 @@ def test_indexer_kl_target_chunks(dev, G, n_q, T, hot):
             assert np.all(err_d <= rel * (np.abs(dref) + np.abs(dref).max()) + 2e-8), f"row {(m, r)}: {err_d.max():.3g}"
             worst = max(worst, err)
     say(f"  worst |loss - ref| {worst:.3g}")
+
+
+# Row-wise selection of 16 and more rows: the candidate counts at which the top-k's register block ends
+# (1024, 2048, 4096 candidates, and past it the radix form), both key grids, ragged units of 64 rows
+# and workgroups of 256, one local block (windows that a row does not see whole) and no initial
+# block.  `levels` > 0 draws scores from so many values, exact in float32, so that ties decide: those sets
+# must be the oracle's, while real scores may exchange near-ties.
+@pytest.mark.parametrize("C,n_q,k,n_init,n_local,grid,levels", [
+    (513, 16, 20, 1, 2, (32, 16), 0), (1024, 70, 64, 1, 2, (64, 64), 0), (1025, 257, 12, 0, 1, (32, 16), 0),
+    (2048, 33, 500, 1, 2, (32, 16), 0), (2049, 65, 64, 2, 3, (64, 64), 0), (4096, 20, 64, 1, 1, (32, 16), 0),
+    (4097, 17, 40, 1, 2, (64, 64), 0), (700, 64, 30, 1, 2, (64, 64), 1), (2048, 40, 64, 1, 2, (64, 64), 3),
+    (1500, 30, 700, 1, 2, (32, 16), 40), (4200, 16, 64, 0, 2, (64, 64), 3)])
+def test_rowwise_select_edges(dev, C, n_q, k, n_init, n_local, grid, levels):
+    say(f"row-wise select C{C} n_q{n_q} k{k} init {n_init} local {n_local} grid {grid} levels {levels}")
+    H, T = 2, 64 * (n_init + C + n_local) - 7  # the last row has C candidates
+    q_pos0, t_cap = T - n_q, -(-T // 64) * 64
+    nw = (T - grid[0]) // grid[1] + 1
+    s, o = shapes(1, H, 4, k, t_cap, nw, n_init, n_local, grid)
+    f = inputs.normal_bf16((1, H, n_q, 128), 7, 0)
+    kc = inputs.normal_bf16((1, H, nw, 128), 7, 1)
+    if levels:  # F = e0 scaled by a power of two, K~'s first component one of `levels` small integers
+        f.zero_()
+        f[..., 0] = 2.0
+        kc[..., 0] = torch.from_numpy(np.random.default_rng(C).integers(0, levels, size=(1, H, nw)).astype(np.float32)).to(kc.dtype)
+    sel = torch.full((1, H, n_q, k), 777, dtype=torch.int16, device=dev)
+    cnt = torch.full((1, H, n_q), 777, dtype=torch.int16, device=dev)
+    ws = torch.empty(sp.sparda_workspace_size(s, sp.SPARDA_OP_FORECAST_SELECT, n_q, q_pos0), dtype=torch.uint8, device=dev)
+    sp.sparda_forecast_select(s, f.to(dev), n_q, q_pos0, kc.to(dev), sel, cnt, ws)
+    torch.cuda.synchronize()
+    sel, cnt = sel.cpu().numpy(), cnt.cpu().numpy()
+    f16, kc16 = inputs.to_u16(f), inputs.to_u16(kc)
+    if levels:
+        ref, rcnt = oracle.forecast_select(o, f16, n_q, q_pos0, kc16)
+        assert np.array_equal(cnt, rcnt) and np.array_equal(sel, ref)
+    else:
+        rows = [(0, m, r) for m in range(H) for r in sorted({0, 1, n_q // 2, n_q - 2, n_q - 1})]
+        say("  rows %d, tie swaps %d" % compare_selection(o, f16, kc16, n_q, q_pos0, sel, cnt, rows))
