@@ -20,14 +20,15 @@
 //                           target's shared weights for 64 / G rows at a time (64 (row, head) columns
 //                           on 32x32x16 MFMA), max-pooled to segments of 16 fine windows in the
 //                           workspace (2 floats per segment instead of one per fine window).
+//   kl_predict_kernel    -- for the same G: F . K~p of 64 rows at a time on MFMA into the workspace.
 //   kl_row_kernel        -- one 512-thread workgroup per query row.  Target: the max-pool of those
 //                           weights into the positions, or for other G 16-window x 16-head
 //                           MFMA tiles (A = the windows, B = the group's query rows padded to 16
 //                           columns), an online maximum and sum of 2^z per head, then a second
 //                           pass that sums each window's normalised head weights across the
 //                           columns and max-pools it into its positions in LDS (atomic max on the
-//                           float bits: all values are >= 0).  Prediction: the Forecast GEMV over
-//                           the positions into LDS and its softmax.  Selection: the block-wide
+//                           float bits: all values are >= 0).  Prediction: the logits of
+//                           kl_predict_kernel (or a Forecast GEMV) and their softmax in LDS.  Selection: the block-wide
 //                           top-k of select_block.hpp over the candidate positions.  Then
 //                           the bucket sums, the loss and the gradient GEMV.
 #include <math.h>
@@ -71,6 +72,7 @@ struct KlArgs {
   float* loss;            // [B][Hkv][n_q]
   float* dF;              // [B][Hkv][n_q][D]
   float* sw;              // [B][Hkv][n_q][sw_stride] segment maxima of the shared target weights (workspace)
+  const float* z;         // [B][Hkv][n_q][sw_stride] prediction logits (exp2 domain; workspace)
   int64_t sw_stride;
   int32_t lds_pos, lds_top;  // per-position LDS entries (>= 512, a multiple of 16) and top-k list entries
   int64_t nt, nc_cap, q_pos0;
@@ -103,6 +105,31 @@ __device__ __forceinline__ float block_max_f(float x, float* red, int wave, int 
 #pragma unroll
   for (int w = 1; w < kDecThreads / 64; ++w) m = fmaxf(m, red[w]);
   return m;
+}
+
+// The prediction's logits (in the exp2 domain) of many rows on MFMA: a unit is 64 rows of one (batch,
+// group) with their one Forecast head (head_tiles.hpp with G = 1), against the prediction positions.
+__global__ __launch_bounds__(kHtThreads, 2) void kl_predict_kernel(HeadTileArgs a) {
+  using namespace head_tiles;
+  __shared__ __align__(16) char slots[2 * kHtSlot];
+  const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
+  const Unit u = unit_of<1>(a);
+  bf16x8 fa[2][8];
+  load_rows<1>(a, u, fa);
+  float* const out = a.out + ((int64_t)u.grp * a.n_q + u.r0) * a.out_stride;
+  walk<1>(a, u, fa, slots, [&](int key0, f32x16 (&c)[2]) {
+    int64_t stride = a.out_stride;
+    __asm__ __volatile__("" : "+s"(stride));  // row addresses here: held across the loop they would spill
+    if (key0 + n >= u.n_keys) return;
+    float* d = out + (int64_t)h * stride + key0 + n;
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int row = 32 * mt + 2 * e;  // of lane half 0
+        if (row + h < u.nr) d[row * stride] = c[mt][e] * a.scale_log2;
+      }
+  });
 }
 
 // kPre: the segment maxima of the target's shared weights are in a.sw (head_weights_kernel); the row
@@ -219,8 +246,12 @@ __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
   }
   __syncthreads();
 
-  // ---- prediction: Forecast GEMV over the positions (16 lanes per position), then its softmax
-  {
+  // ---- prediction: the row's logits, from kl_predict_kernel or a Forecast GEMV over the positions (16
+  // lanes per position), then its softmax
+  if (kPre) {
+    const float* z = a.z + row * a.sw_stride;
+    for (int w = tid; w < N; w += kDecThreads) Pp[w] = z[w];
+  } else {
     const int c = lane & 15, rs = lane >> 4;
     float fv[8];
     {
@@ -300,21 +331,48 @@ __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
   kl = block_sum_f(kl, red, wave, lane);
   if (tid == 0) a.loss[row] = kl + (t_rest > 0.f ? t_rest * __logf(t_rest / R) : 0.f);
 
-  // ---- gradient: dF[d] = sm_scale sum_w g_w K~p_w[d]; thread (grp, d): positions w = grp mod 4
+  // ---- gradient: dF[d] = sm_scale sum_w g_w K~p_w[d].  The weights g replace P in LDS; lane l of
+  // wavefront v takes dimensions 8 (l % 16) .. + 7 of positions 4 (v + 8 i) + l / 16, so a wavefront
+  // load is 1 KiB of K~p and a position's weight one LDS read for 16 lanes (a 2-byte load, two LDS reads
+  // and a flag per product before: 270 of the 785 us of the kernel at 2048 rows of 4094 positions).
   const float rest_f = R > 0.f ? 1.0f - t_rest / R : 0.f;
+  for (int w = tid; w < N; w += kDecThreads) Pp[w] = chosen[w] ? Pp[w] - Tp[w] * tinv : Pp[w] * rest_f;
+  __syncthreads();
   {
-    const int d = tid & 127, grp = tid >> 7;
-    const uint16_t* kpb = a.kp + bm * a.nc_cap * kHeadDim + d;
-    float acc = 0.f;
-    for (int w = grp; w < N; w += 4) {
-      const float g = chosen[w] ? Pp[w] - Tp[w] * tinv : Pp[w] * rest_f;
-      const uint16_t kv = kpb[(int64_t)w * kHeadDim];
-      acc = fmaf(g, __uint_as_float((uint32_t)kv << 16), acc);
+    const int c = lane & 15, rs = lane >> 4;
+    const uint16_t* kpb = a.kp + bm * a.nc_cap * kHeadDim + 8 * c;
+    float acc[8] = {};
+    for (int base = wave * 4; base < N; base += (kDecThreads / 64) * 4) {
+      const int w = base + rs;
+      const uint4 k = ld16(kpb + (int64_t)min(w, N - 1) * kHeadDim);
+      const float g = w < N ? Pp[w] : 0.f;
+      acc[0] = fmaf(g, bf16lo(k.x), acc[0]);
+      acc[1] = fmaf(g, bf16hi(k.x), acc[1]);
+      acc[2] = fmaf(g, bf16lo(k.y), acc[2]);
+      acc[3] = fmaf(g, bf16hi(k.y), acc[3]);
+      acc[4] = fmaf(g, bf16lo(k.z), acc[4]);
+      acc[5] = fmaf(g, bf16hi(k.z), acc[5]);
+      acc[6] = fmaf(g, bf16lo(k.w), acc[6]);
+      acc[7] = fmaf(g, bf16hi(k.w), acc[7]);
     }
-    __syncthreads();
-    Tp[tid] = acc;  // the target scores are no longer needed
-    __syncthreads();
-    if (tid < 128) a.dF[row * kHeadDim + tid] = a.sm_scale * (Tp[tid] + Tp[tid + 128] + Tp[tid + 256] + Tp[tid + 384]);
+    // the wavefront's four position residues, then the wavefronts through LDS (the target scores are no
+    // longer needed: at least 512 floats, so two rounds of four wavefronts)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      acc[i] += __shfl_xor(acc[i], 16, kWave);
+      acc[i] += __shfl_xor(acc[i], 32, kWave);
+    }
+    float sum = 0.f;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      __syncthreads();
+      if (wave / 4 == half && rs == 0)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) Tp[(wave & 3) * kHeadDim + 8 * c + i] = acc[i];
+      __syncthreads();
+      if (tid < kHeadDim) sum += Tp[tid] + Tp[tid + 128] + Tp[tid + 256] + Tp[tid + 384];
+    }
+    if (tid < kHeadDim) a.dF[row * kHeadDim + tid] = a.sm_scale * sum;
   }
 }
 
@@ -377,6 +435,25 @@ hipError_t launch_indexer_kl(const uint16_t* q, const uint16_t* k, const uint16_
     t.scale_log2 = a.scale_log2;
     plan_head_tiles(t, G, kHeadDim / (2 * G));
     hipError_t e = launch_head_tiles<head_tiles::kSegments>(t, G, stream);
+    if (e != hipSuccess) return e;
+    // the logits of a row's positions after its segment maxima: of the fine windows' nt floats per row
+    // the maxima take 2 per 16 and the logits 1 per 16 or 64
+    a.z = sw_ws + 2 * ((a.nt + 15) / 16);
+    HeadTileArgs z = {};
+    z.q = f;
+    z.keys = kp;
+    z.key_cap = nc_cap;
+    z.out = const_cast<float*>(a.z);
+    z.out_stride = a.sw_stride;
+    z.q_pos0 = q_pos0;
+    z.n_groups = (int32_t)rows_g;
+    z.n_q = n_q;
+    z.grid = grid;
+    z.scale_log2 = a.scale_log2;
+    plan_head_tiles(z, 1, 64);
+    hipLaunchKernelGGL(kl_predict_kernel, dim3((unsigned)((int64_t)z.n_groups * z.n_wg * z.n_chunks)), dim3(kHtThreads),
+                       0, stream, z);
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kl_row_kernel<true>, dim3((unsigned)(rows_g * n_q)), dim3(kDecThreads), lds, stream, a);
   } else {
