@@ -14,8 +14,9 @@
 //    pooled block scores, score_max.hip); a second kernel runs one wavefront per row that finds the
 //    exact k-th key by counts over keys in registers (up to 4096 candidates) or an 8-bit-digit radix
 //    select over a wave-private LDS histogram, and emits the chosen indices in ascending order.
-//  * fused decode (one row per (batch, group), <= 16384 candidates): one workgroup per row keeps
-//    the row's scores in LDS and runs the block-wide top-k there (select_block.hpp).
+//  * fused decode (one row per (batch, group), <= 16384 candidates, and multi-row calls of few rows):
+//    one workgroup per row keeps the row's scores in LDS and runs the block-wide top-k there
+//    (select_block.hpp).
 //  * fused tile (multi-row prefill with <= 512 candidates per 64-row tile): select_prefill.hip.
 #include "device_util.hpp"
 #include "launch.hpp"
@@ -288,7 +289,12 @@ __global__ __launch_bounds__(kDecThreads) void decode_select_kernel(SelectArgs a
   __shared__ __align__(16) uint32_t hist[kTopkLds];
   __shared__ int wave_cnt[kDecThreads / 64];
   __shared__ int pick[3];
-  const int64_t row = blockIdx.x;
+  // workgroup x takes row x / n_groups of group x % n_groups, so that (with 8 | n_groups) the rows of a
+  // group share an XCD's L2
+  const int64_t n_groups = (int64_t)a.batch * a.n_kv_heads;
+  const int64_t bm = blockIdx.x % n_groups, r = blockIdx.x / n_groups, row = bm * a.n_q + r;
+  a.q_pos0 += r;
+  a.kc += (bm - row) * a.nc_cap * kHeadDim;  // the row's keys, where decode_select_row looks for them
   decode_select_row(a, row, sc, hist, wave_cnt, pick, a.sel + row * a.k_total, a.cnt + row);
 }
 
@@ -311,6 +317,15 @@ enum SelectPath { kPathDecode, kPathDecodeSplit, kPathTile, kPathRowwise };
 // kernel, 256 windows each) and select with one workgroup per row; otherwise one fused workgroup
 // per row.
 constexpr int64_t kDecodeSplitRows = 256;
+// Multi-row calls of few rows (verifying drafted tokens, the tail of a prompt) select like decode rows,
+// one workgroup per row: at most two rows per CU, of at most the windows that a full tile row has.
+// Measured, 80 to 4096 rows (us, this path against the tile kernels or, past 512 candidates, the
+// row-wise path): (64, 64) grid at 20K 8, 14, 26, 50 for 256, 512, 1024, 2048 rows against 22-24 for
+// any number; (32, 16) grid at 20K 13, 24, 46 for 256, 512, 1024 rows against 35-39, at 32K 17, 32, 61
+// against 55-80; (64, 64) grid at 64K 12 and 22 for 256 and 512 rows against 20-36.  At 4060 windows per
+// row ((32, 16) grid at 64K) 27 and 52 against 23-39.
+constexpr int64_t kFewRows = 512;
+constexpr int64_t kFewRowsWindows = 4 * kSelTileMaxCand + 1;
 // Multi-row calls on the row-wise path with at least this many rows score on MFMA.
 constexpr int32_t kTileScoreMinRows = 16;
 
@@ -323,11 +338,13 @@ static SelectPath select_path(int64_t rows, int32_t n_q, int64_t q_pos0, int32_t
   int32_t wf, wl;
   row_windows(g, grid, p, &wf, &wl);
   const int64_t nw = wl >= wf ? wl - wf + 1 : 0;
-  if (n_q == 1) {  // window scores and (for a windowed grid) block scores share the LDS score array
-    const int64_t need = grid_is_blocks(grid) ? g.n_cand : nw + g.n_cand;
+  // window scores and (for a windowed grid) block scores share the LDS score array
+  const int64_t need = grid_is_blocks(grid) ? g.n_cand : nw + g.n_cand;
+  if (n_q == 1) {
     if (need > kDecodeMaxCand) return kPathRowwise;
     return rows < kDecodeSplitRows && nw >= 1024 ? kPathDecodeSplit : kPathDecode;
   }
+  if (rows <= kFewRows && nw <= kFewRowsWindows) return kPathDecode;  // at most 2561 floats
   // multi-row: the fused tile kernel serves both grids up to kSelTileMaxCand candidates per row
   return tile_grid(grid) && g.n_cand <= kSelTileMaxCand ? kPathTile : kPathRowwise;
 }

@@ -151,3 +151,29 @@ def test_rowwise_select_edges(dev, C, n_q, k, n_init, n_local, grid, levels):
     else:
         rows = [(0, m, r) for m in range(H) for r in sorted({0, 1, n_q // 2, n_q - 2, n_q - 1})]
         say("  rows %d, tie swaps %d" % compare_selection(o, f16, kc16, n_q, q_pos0, sel, cnt, rows))
+
+
+# Multi-row calls of few rows select one workgroup per row: the last row count and window count of that
+# rule and the first past them, groups that do and do not divide 8, a chunk that begins before the first
+# candidate exists.
+@pytest.mark.parametrize("B,H,n_q,T,grid", [(1, 3, 2, 20011, (32, 16)), (2, 4, 64, 9000, (64, 64)), (2, 4, 65, 9000, (64, 64)),
+                                            (1, 1, 100, 140, (32, 16)), (1, 2, 17, 64 * 515 - 1, (32, 16)),
+                                            (1, 2, 17, 64 * 516, (32, 16)), (1, 2, 5, 64 * 2052, (64, 64)),
+                                            (1, 2, 5, 64 * 2053, (64, 64))])
+def test_few_rows_select(dev, B, H, n_q, T, grid):
+    say(f"few rows select B{B} H{H} n_q{n_q} T{T} grid {grid}")
+    k, q_pos0, t_cap = 24, T - n_q, -(-T // 64) * 64
+    nw = (T - grid[0]) // grid[1] + 1
+    s, o = shapes(B, H, 4, k, t_cap, nw, 1, 2, grid)
+    f = inputs.normal_bf16((B, H, n_q, 128), 8, 0)
+    kc = inputs.normal_bf16((B, H, nw, 128), 8, 1)
+    sel = torch.full((B, H, n_q, k), 777, dtype=torch.int16, device=dev)
+    cnt = torch.full((B, H, n_q), 777, dtype=torch.int16, device=dev)
+    ws = torch.empty(max(sp.sparda_workspace_size(s, sp.SPARDA_OP_FORECAST_SELECT, n_q, q_pos0), 16), dtype=torch.uint8,
+                     device=dev)
+    sp.sparda_forecast_select(s, f.to(dev), n_q, q_pos0, kc.to(dev), sel, cnt, ws)
+    torch.cuda.synchronize()
+    rows = [(b, m, r) for b in range(B) for m in range(H) for r in sorted({0, 1, n_q // 2, n_q - 1})]
+    n, swaps = compare_selection(o, inputs.to_u16(f), inputs.to_u16(kc), n_q, q_pos0, sel.cpu().numpy(), cnt.cpu().numpy(),
+                                 rows)
+    say(f"  rows {n}, tie swaps {swaps}")
