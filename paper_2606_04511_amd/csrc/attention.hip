@@ -311,21 +311,31 @@ __global__ __launch_bounds__(NW * 64) void decode_step_kernel(SelectArgs s, Attn
 
 // Decode attention for groups of 6 to 16 heads: P V on MFMA.  With this many query rows per
 // block the VALU P V of sparse_attn_kernel (G x 8 FMAs per token per lane) no longer hides under
-// the loads, while P V fills a 16-column MFMA tile.  Per 64-token block a wavefront:
-//   * loads K and V as sparse_attn_kernel does and computes S^T = K Q^T (lane (n, g) holds
-//     head n's scores of tokens 16 tt + 4 g + i);
-//   * stages V in its LDS slice (272-byte rows; tokens after p are zeroed) and computes
-//     O^T += V^T P^T on v_mfma_f32_16x16x32_bf16 in two 32-token chunks: the B operand of chunk c
-//     is lane (n, g)'s own probabilities of tiles 2c and 2c + 1 rounded to bf16 (k = 8 g + j holds
-//     token 16 (2 c + j / 4) + 4 g + j % 4), the A operand (dims x those tokens) is read from LDS;
+// the loads, while P V fills a 16-column MFMA tile.  A wavefront walks its blocks in halves of 32
+// tokens, whose 8 KiB of K and 8 KiB of V go from memory straight into two LDS buffers of its own (1 KiB
+// per instruction, whole token rows), so the next half's K is in flight from the moment the
+// products of this one have read K, and its V from the moment O has read V; the wavefront waits for its
+// own loads by count and no barrier joins the wavefronts until the merge.  Per half:
+//   * S^T = K Q^T (lane (n, g) holds head n's scores of tokens 16 tt + 4 g + i, tt = 0, 1);
+//   * O^T += V^T P^T on v_mfma_f32_16x16x32_bf16: the B operand is the lane's own probabilities
+//     rounded to bf16 (k = 8 g + j holds token 16 (j / 4) + 4 g + j % 4), the A operand (dims x those
+//     tokens) comes from the transposing LDS read; tokens after p are zeroed in LDS first;
 //   * the softmax denominator sums the same bf16-rounded probabilities.
+// The rows' 16-byte pieces lie XOR-swizzled in LDS (the load's LDS side is linear, so a lane asks for
+// another piece of its row): piece x of token t at x ^ (t % 16) for K, x ^ 2 (t % 8) for V.
 // Lane (n, g) accumulates dims 16 dt + 4 g + e of head n in o[dt]; the wavefronts' states merge
-// through LDS (the V slices' space) as in sparse_attn_kernel.
-constexpr int kWidePitch = 136;  // uint16 per staged V row (272 B: 16-byte aligned, bank-spread)
+// through LDS (the buffers' space) as in sparse_attn_kernel.
+//
+// What bounds it: the memory stream and what frames it (selection, first loads, merge).  The step of the
+// paper's layout at 128K, batch 32 (201 MB of K and V, 64 rows, four splits): 46.6 us; with K and V
+// through registers, V gathered from LDS two bytes at a time and library exp2 and rounding 51.7 us.  80
+// rows of 7 heads, 48 blocks each: 29.6 us, 35.6 before.
+constexpr int kWideHalf = 32;                                // tokens per half block
+constexpr int kWideBuf = kWideHalf * kHeadDim * 2;           // bytes of a half's K or V
 
-// LDS of one workgroup of the wide kernel: the V slices (also the wavefronts' merge space).
+// LDS of one workgroup of the wide kernel: each wavefront's K and V buffers (also the merge space).
 struct WideLds {
-  uint16_t vst[kAttnWaves][kBlock * kWidePitch];
+  char kv[kAttnWaves][2][kWideBuf];
 };
 
 // The wide kernel's attention of query row `row`, split `split`, over srow (a.k_total entries,
@@ -334,8 +344,7 @@ template <int G>
 __device__ __forceinline__ void attend_row_wide(const AttnArgs& a, int64_t row, int split, WideLds& L,
                                                 const int16_t* srow, int n_listed) {
   constexpr int NW = kAttnWaves;
-  auto& vst = L.vst;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = (int)(row % a.n_q);
   const int64_t bm = row / a.n_q;
   const int m = (int)(bm % a.n_kv_heads);
@@ -349,6 +358,55 @@ __device__ __forceinline__ void attend_row_wide(const AttnArgs& a, int64_t row, 
   const float zscale = a.sm_scale * kLog2e;
   const int hh = lane & 15;   // head (S^T column, O^T column)
   const int grp = lane >> 4;  // k-chunk of the QK operands; token group of P; dim group of O^T
+  const char* kbuf = L.kv[wave][0];
+  const char* vbuf = L.kv[wave][1];
+  const uint32_t k_at = __builtin_amdgcn_readfirstlane(lds_address(kbuf));
+  const uint32_t v_at = k_at + kWideBuf;
+
+  // The row's first 128 entries stay in registers.
+  const int e0 = lane < n ? (int)srow[lane] : -1, e1 = 64 + lane < n ? (int)srow[64 + lane] : -1;
+  // The next of this wavefront's entries from s on that names a block up to the row's own which no
+  // earlier entry lists (s_end: none); its block in *j.
+  auto find = [&](int s, int* j) {
+    for (; s < s_end; s += NW) {
+      const int x = s < 64 ? readlane_i(e0, s) : s < 128 ? readlane_i(e1, s - 64)
+                                                         : __builtin_amdgcn_readfirstlane((int)srow[s]);
+      if (x < 0 || x > blk) continue;
+      bool dup = __ballot((lane < s && e0 == x) || (64 + lane < s && e1 == x)) != 0ull;
+      for (int b0 = 128; b0 < s; b0 += 64) {
+        const int e = b0 + lane;
+        dup |= __ballot(e < s && (int)srow[e] == x) != 0ull;
+      }
+      if (dup) continue;
+      *j = x;
+      break;
+    }
+    return min(s, s_end);
+  };
+  // 8 instructions of 4 token rows each: half `hf` of entry s, block j, of the cache at `base`
+  const int r4 = lane >> 4;
+  const uint32_t k_off = r4 * 256 + 16 * ((lane & 15) ^ r4), v_off = r4 * 256 + 16 * ((lane & 15) ^ (2 * r4));
+  auto half_at = [&](const uint16_t* cache, int s, int j, int hf) {
+    const int64_t blk_row = a.kv_mode == 0 ? bm * a.t_cap + (int64_t)j * kBlock : (bm * a.k_total + s) * kBlock;
+    return reinterpret_cast<const char*>(cache + (blk_row + hf * kWideHalf) * kHeadDim);
+  };
+  auto issue_k = [&](int s, int j, int hf) {
+    const char* src = half_at(a.k, s, j, hf);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) lds_load16(src + 1024 * i, k_off ^ ((i & 3) << 6), k_at + 1024 * i);
+  };
+  auto issue_v = [&](int s, int j, int hf) {
+    const char* src = half_at(a.v, s, j, hf);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) lds_load16(src + 1024 * i, v_off ^ ((i & 1) << 7), v_at + 1024 * i);
+  };
+
+  int j = 0, hf = 0;
+  int s = find(s_begin + wave, &j);
+  if (s < s_end) {
+    issue_k(s, j, 0);
+    issue_v(s, j, 0);
+  }
   bf16x8 qb[4];
   {  // columns past the group's heads read head 0 (a valid address) and are zeroed
     const uint16_t* qrow =
@@ -363,69 +421,56 @@ __device__ __forceinline__ void attend_row_wide(const AttnArgs& a, int64_t row, 
   f32x4 o[8];
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  uint16_t* vs = vst[wave];
+  // operand addresses: K row 16 tt + hh, piece (4 ks + grp) ^ hh; V rows 16 x + 4 grp + hh / 4, dims
+  // 16 dt + 4 (hh % 4) .. + 3
+  const uint32_t ka = hh * 256 + 16 * (grp ^ hh);
+  const int vt = 4 * grp + (hh >> 2);
+  const uint32_t va = vt * 256 + 16 * (((hh >> 1) & 1) ^ (2 * (vt & 7))) + 8 * (hh & 1);
+  lds_loads_landed();  // the first half, and the query rows: from here on the loads are counted
 
-  const int entry = lane < n ? (int)srow[lane] : -1;
-  for (int s = s_begin + wave; s < s_end; s += NW) {
-    const int j = __builtin_amdgcn_readfirstlane((int)srow[s]);
-    if (j < 0 || j > blk) continue;
-    bool dup = __ballot(lane < s && entry == j) != 0ull;
-    for (int e0 = 64; e0 < s; e0 += 64) {
-      const int e = e0 + lane;
-      dup |= __ballot(e < s && (int)srow[e] == j) != 0ull;
+  while (s < s_end) {
+    const int last = (j == blk ? (int)(p - (int64_t)j * kBlock) : kBlock - 1) - hf * kWideHalf;  // >= 0
+    // what follows: the block's second half where it holds visible tokens, or the next entry
+    int s2 = s, j2 = j, hf2 = 1;
+    if (hf == 1 || last < kWideHalf) {
+      hf2 = 0;
+      s2 = find(s + NW, &j2);
     }
-    if (dup) continue;
-    const int64_t base = a.kv_mode == 0 ? (bm * a.t_cap + (int64_t)j * kBlock) * kHeadDim
-                                        : ((bm * a.k_total + s) * kBlock) * kHeadDim;
-    const uint16_t* kb = a.k + base;
-    const uint16_t* vb = a.v + base;
-    uint4 kw[4][4];
+    const bool more = s2 < s_end;
+    __asm__ __volatile__("s_waitcnt vmcnt(8)" ::: "memory");  // this half's K (its V may be under way)
+    f32x4 st[2];
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) kw[tt][ks] = ld16(kb + (16 * tt + hh) * kHeadDim + 32 * ks + 8 * grp);
-    uint4 vw[16];
-#pragma unroll
-    for (int it = 0; it < 16; ++it) vw[it] = ld16(vb + (4 * it + grp) * kHeadDim + 8 * hh);
-
-    f32x4 st[4];
-#pragma unroll
-    for (int tt = 0; tt < 4; ++tt) {
+    for (int tt = 0; tt < 2; ++tt) {
       st[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) st[tt] = mfma16x16x32(as_bf16x8(kw[tt][ks]), qb[ks], st[tt]);
+      for (int ks = 0; ks < 4; ++ks)
+        st[tt] = mfma16x16x32(as_bf16x8(*reinterpret_cast<const uint4*>(kbuf + 4096 * tt + (ka ^ (ks << 6)))), qb[ks], st[tt]);
     }
-    const int last = (j == blk) ? (int)(p - (int64_t)j * kBlock) : kBlock - 1;
-    // V into the wavefront's LDS slice, tokens after p as zeros (their values are not written)
-#pragma unroll
-    for (int it = 0; it < 16; ++it) {
-      const int tok = 4 * it + grp;
-      *reinterpret_cast<uint4*>(vs + tok * kWidePitch + 8 * hh) = tok <= last ? vw[it] : make_uint4(0u, 0u, 0u, 0u);
-    }
-    float z[4][4];
+    __asm__ __volatile__("s_waitcnt lgkmcnt(0)" ::: "memory");  // K has been read
+    if (more) issue_k(s2, j2, hf2);
+    float z[2][4];
     float bmax = -INFINITY;
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
+    for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int tok = 16 * tt + 4 * grp + i;
-        z[tt][i] = tok <= last ? st[tt][i] * zscale : -INFINITY;
+        z[tt][i] = 16 * tt + 4 * grp + i <= last ? st[tt][i] * zscale : -INFINITY;
         bmax = fmaxf(bmax, z[tt][i]);
       }
     bmax = fmaxf(bmax, __shfl_xor(bmax, 16, 64));
     bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-    const float m_new = fmaxf(m_run, bmax);  // token 0 of a block is always <= p: finite
-    const float alpha = exp2f(m_run - m_new);
-    uint32_t pw[4][2];  // bf16 pairs of tile tt: (i = 0, 1), (i = 2, 3)
+    const float m_new = fmaxf(m_run, bmax);  // the half's first token is always <= p: finite
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    uint32_t pw[2][2];  // bf16 pairs of tile tt: (i = 0, 1), (i = 2, 3)
     float psum = 0.f;
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
+    for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
       for (int q2 = 0; q2 < 2; ++q2) {
-        const uint16_t lo = f32_to_bf16(exp2f(z[tt][2 * q2] - m_new));
-        const uint16_t hi = f32_to_bf16(exp2f(z[tt][2 * q2 + 1] - m_new));
-        psum += __uint_as_float((uint32_t)lo << 16) + __uint_as_float((uint32_t)hi << 16);
-        pw[tt][q2] = (uint32_t)lo | ((uint32_t)hi << 16);
+        const uint32_t w = pack_bf16(__builtin_amdgcn_exp2f(z[tt][2 * q2] - m_new),
+                                     __builtin_amdgcn_exp2f(z[tt][2 * q2 + 1] - m_new));
+        psum += bf16lo(w) + bf16hi(w);
+        pw[tt][q2] = w;
       }
     psum += __shfl_xor(psum, 16, 64);
     psum += __shfl_xor(psum, 32, 64);
@@ -433,33 +478,33 @@ __device__ __forceinline__ void attend_row_wide(const AttnArgs& a, int64_t row, 
     m_run = m_new;
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) o[dt] *= alpha;
-    wave_lds_sync();
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const bf16x8 pb = as_bf16x8(make_uint4(pw[2 * c][0], pw[2 * c][1], pw[2 * c + 1][0], pw[2 * c + 1][1]));
-      // A rows: dim 16 dt + hh; k = 8 grp + jj -> token 16 (2 c + jj / 4) + 4 grp + jj % 4
-      const uint16_t* r0 = vs + (16 * (2 * c) + 4 * grp) * kWidePitch + hh;
-      const uint16_t* r1 = vs + (16 * (2 * c + 1) + 4 * grp) * kWidePitch + hh;
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt) {
-        uint32_t aw[4];
-#pragma unroll
-        for (int q2 = 0; q2 < 2; ++q2) {
-          aw[q2] = (uint32_t)r0[(2 * q2) * kWidePitch + 16 * dt] | ((uint32_t)r0[(2 * q2 + 1) * kWidePitch + 16 * dt] << 16);
-          aw[2 + q2] =
-              (uint32_t)r1[(2 * q2) * kWidePitch + 16 * dt] | ((uint32_t)r1[(2 * q2 + 1) * kWidePitch + 16 * dt] << 16);
-        }
-        o[dt] = mfma16x16x32(as_bf16x8(make_uint4(aw[0], aw[1], aw[2], aw[3])), pb, o[dt]);
-      }
+    if (more)
+      __asm__ __volatile__("s_waitcnt vmcnt(8)" ::: "memory");  // this half's V (the next K may be under way)
+    else
+      __asm__ __volatile__("s_waitcnt vmcnt(0)" ::: "memory");
+    if (last < kWideHalf - 1) {  // tokens after p: whatever the cache holds there becomes zeros
+      for (int t = last + 1 + r4; t < kWideHalf; t += 4)
+        *reinterpret_cast<uint4*>(L.kv[wave][1] + t * 256 + 16 * (lane & 15)) = make_uint4(0u, 0u, 0u, 0u);
+      wave_lds_sync();
     }
-    wave_lds_sync();
+    const bf16x8 pb = as_bf16x8(make_uint4(pw[0][0], pw[0][1], pw[1][0], pw[1][1]));
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) {
+      const uint2 v0 = lds_read_tr16(vbuf + (va ^ (dt << 5))), v1 = lds_read_tr16(vbuf + 4096 + (va ^ (dt << 5)));
+      o[dt] = mfma16x16x32(as_bf16x8(make_uint4(v0.x, v0.y, v1.x, v1.y)), pb, o[dt]);
+    }
+    __asm__ __volatile__("s_waitcnt lgkmcnt(0)" ::: "memory");  // V has been read
+    if (more) issue_v(s2, j2, hf2);
+    s = s2;
+    j = j2;
+    hf = hf2;
   }
 
-  // Merge the wavefronts' states through the V slices' space.
+  // Merge the wavefronts' states through the buffers' space.
   __syncthreads();
-  float* st_m = reinterpret_cast<float*>(&vst[0][0]);  // [NW][16]
-  float* st_l = st_m + NW * 16;                         // [NW][16]
-  float* st_acc = st_l + NW * 16;                       // [NW][16][128]
+  float* st_m = reinterpret_cast<float*>(&L.kv[0][0][0]);  // [NW][16]
+  float* st_l = st_m + NW * 16;                               // [NW][16]
+  float* st_acc = st_l + NW * 16;                             // [NW][16][128]
   if (grp == 0) {
     st_m[wave * 16 + hh] = m_run;
     st_l[wave * 16 + hh] = l_run;
@@ -510,7 +555,7 @@ __global__ __launch_bounds__(kAttnWaves * 64) void sparse_attn_wide_kernel(AttnA
 template <int G, bool kSplitSel>
 __global__ __launch_bounds__(kAttnWaves * 64) void decode_step_wide_kernel(SelectArgs s, AttnArgs a) {
   static_assert(kAttnWaves * 64 == kDecThreads, "the selection runs on the attention workgroup");
-  static_assert(sizeof(float) * kDecodeMaxCand <= sizeof(WideLds), "scores fit in the V slices");
+  static_assert(sizeof(float) * kDecodeMaxCand <= sizeof(WideLds), "scores fit in the K and V buffers");
   __shared__ __align__(16) WideLds lds;
   __shared__ __align__(16) uint32_t hist[kTopkLds];
   __shared__ int wave_cnt[kDecThreads / 64];
@@ -518,7 +563,7 @@ __global__ __launch_bounds__(kAttnWaves * 64) void decode_step_wide_kernel(Selec
   __shared__ __align__(16) int16_t set[kStepMaxK];
   __shared__ int16_t set_cnt;
   const int64_t row = blockIdx.x;
-  step_select<kSplitSel>(s, row, reinterpret_cast<float*>(&lds.vst[0][0]), hist, wave_cnt, pick, set, &set_cnt);
+  step_select<kSplitSel>(s, row, reinterpret_cast<float*>(&lds.kv[0][0][0]), hist, wave_cnt, pick, set, &set_cnt);
   attend_row_wide<G>(a, row, blockIdx.y, lds, set, set_cnt);
 }
 

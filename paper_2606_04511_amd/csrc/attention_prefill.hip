@@ -60,21 +60,6 @@ constexpr int kPaStaticLds = 2 * kPaSlot + 16;      // the two slots, n_union
 constexpr int kPaLdsMax = 160 * 1024;      // LDS of one CU
 constexpr float kLog2eP = 1.4426950408889634f;
 
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-  const bf16x2 h = __builtin_convertvector(f32x2{lo, hi}, bf16x2);
-  return __builtin_bit_cast(uint32_t, h);
-}
-
-// Transposing LDS read: in each 16 lanes, lane 4 r + x addresses 4 consecutive bf16 of row r, columns
-// 4 x .. 4 x + 3; lane i receives column i of rows 0..3.
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint2 lds_read_tr16(const char* src) {
-  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)src));
-}
-
 // Row bitmaps, union bitmap and union list live in dynamic LDS sized by the call (its last row's
 // causal blocks): wc words per row bitmap.
 __host__ __device__ inline int pa_dyn_lds_bytes(int rows, int nbt) {

@@ -55,6 +55,15 @@ __device__ __forceinline__ uint16_t f64_to_bf16(double x) {
   return (uint16_t)(sign | (uint16_t)q);
 }
 
+// Two floats to a pair of bf16, nearest even.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  const bf16x2 h = __builtin_convertvector(f32x2{lo, hi}, bf16x2);
+  return __builtin_bit_cast(uint32_t, h);
+}
+
 // Order-preserving map of a float score to uint32 (larger score -> larger key); -0 maps like +0.
 __device__ __forceinline__ uint32_t score_key(float s) {
   uint32_t u = __float_as_uint(s == 0.0f ? 0.0f : s);
@@ -217,10 +226,19 @@ __device__ __forceinline__ void lds_load16(const void* base, uint32_t off, uint3
 }
 // Waits for every such load (and every other memory access) of the wavefront.
 __device__ __forceinline__ void lds_loads_landed() {
-  __asm__ __volatile__("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __asm__ __volatile__("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0); the compiler sees it and drops its own waits
+  __asm__ __volatile__("" ::: "memory");
 }
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
+}
+
+// Transposing LDS read: in each 16 lanes, lane 4 r + x addresses 4 consecutive bf16 of row r, columns
+// 4 x .. 4 x + 3; lane i receives column i of rows 0..3.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint2 lds_read_tr16(const char* src) {
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)src));
 }
 
 // z with P(Z > z) = p for a standard normal Z (rational approximation of Abramowitz and Stegun
