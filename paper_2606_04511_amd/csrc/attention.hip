@@ -31,6 +31,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kAttnWaves = 8;        // wavefronts per attention workgroup
 constexpr int kRowsFillChip = 256;   // rows at which one workgroup per row fills 256 CUs
 constexpr int kMaxSplits = 64;
+constexpr int kCombineThreads = 256;
 constexpr int kKstPitch = kHeadDim + 16;  // uint16 per staged K row (288 B)
 constexpr int kStepMaxK = 1024;           // largest k_total of the fused decode step (its set lives in LDS)
 
@@ -567,12 +568,14 @@ __global__ __launch_bounds__(kAttnWaves * 64) void decode_step_wide_kernel(Selec
   attend_row_wide<G>(a, row, blockIdx.y, lds, set, set_cnt);
 }
 
-// Merge the split partials of one (row, head) by log-sum-exp: 128 threads, one per head dim.
+// Merge the split partials of one (row, head) by log-sum-exp: one wavefront, two head dims per lane.
+// Latency is all it costs (a few KB per head), so up to 8 splits' statistics and accumulators are
+// requested at once, without a barrier.
 template <int G>
-__global__ __launch_bounds__(128) void attn_combine_kernel(AttnArgs a) {
-  __shared__ float w_s[kMaxSplits], l_s[kMaxSplits];
-  __shared__ float total_l;
-  const int64_t rh = blockIdx.x;
+__global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(AttnArgs a, int64_t n_heads) {
+  const int lane = threadIdx.x & 63;
+  const int64_t rh = (int64_t)blockIdx.x * (kCombineThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (rh >= n_heads) return;
   const int64_t row = rh / G;
   const int h = (int)(rh % G);
   const int r = (int)(row % a.n_q);
@@ -580,39 +583,39 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(AttnArgs a) {
   const int m = (int)(bm % a.n_kv_heads);
   const int b = (int)(bm / a.n_kv_heads);
   const int64_t Hq = (int64_t)a.n_kv_heads * G;
-  const int tid = threadIdx.x;
   const int64_t stride = (int64_t)G * (kHeadDim + 2);
   const float* base = a.ws + (row * a.n_splits * G + h) * (kHeadDim + 2);
-  const int ns = a.n_splits;  // <= kMaxSplits
-  for (int s = tid; s < ns; s += 128) {
-    w_s[s] = base[s * stride];
-    l_s[s] = base[s * stride + 1];
-  }
-  __syncthreads();
-  if (tid < 64) {
-    float M = -INFINITY;
-    for (int s = tid; s < ns; s += 64) M = fmaxf(M, w_s[s]);
+  float M = -INFINITY, L = 0.f, A0 = 0.f, A1 = 0.f;
+  for (int s0 = 0; s0 < a.n_splits; s0 += 8) {
+    float pm[8], pl[8];
+    float2 pa[8];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
-    float L = 0.f;
-    for (int s = tid; s < ns; s += 64) {
-      const float ms = w_s[s];
-      const float wgt = (M == -INFINITY || ms == -INFINITY) ? 0.f : exp2f(ms - M);
-      w_s[s] = wgt;
-      L = fmaf(l_s[s], wgt, L);
+    for (int i = 0; i < 8; ++i) {
+      const float* src = base + min(s0 + i, a.n_splits - 1) * stride;
+      pm[i] = s0 + i < a.n_splits ? src[0] : -INFINITY;
+      pl[i] = src[1];
+      pa[i] = *reinterpret_cast<const float2*>(src + 2 + 2 * lane);
     }
+    float mx = M;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) L += __shfl_xor(L, o, 64);
-    if (tid == 0) total_l = L;
+    for (int i = 0; i < 8; ++i) mx = fmaxf(mx, pm[i]);
+    if (mx == -INFINITY) continue;
+    const float keep = __builtin_amdgcn_exp2f(M - mx);
+    L *= keep;
+    A0 *= keep;
+    A1 *= keep;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (pm[i] == -INFINITY) continue;  // a split without a token: its accumulators are not written
+      const float w = __builtin_amdgcn_exp2f(pm[i] - mx);
+      L = fmaf(pl[i], w, L);
+      A0 = fmaf(pa[i].x, w, A0);
+      A1 = fmaf(pa[i].y, w, A1);
+    }
+    M = mx;
   }
-  __syncthreads();
-  float A = 0.f;
-  for (int s = 0; s < ns; ++s) {
-    const float wgt = w_s[s];
-    if (wgt != 0.f) A = fmaf(base[s * stride + 2 + tid], wgt, A);
-  }
-  const float L = total_l;
-  a.o[(((int64_t)b * Hq + (int64_t)m * G + h) * a.n_q + r) * kHeadDim + tid] = f32_to_bf16(L > 0.f ? A / L : 0.f);
+  uint32_t* o = reinterpret_cast<uint32_t*>(a.o + (((int64_t)b * Hq + (int64_t)m * G + h) * a.n_q + r) * kHeadDim);
+  o[lane] = (uint32_t)f32_to_bf16(L > 0.f ? A0 / L : 0.f) | ((uint32_t)f32_to_bf16(L > 0.f ? A1 / L : 0.f) << 16);
 }
 
 void attn_plan(int64_t rows, int32_t k_total, int32_t* n_splits, int32_t* blocks_per_split) {
@@ -646,7 +649,8 @@ static hipError_t launch_g(const AttnArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL((sparse_attn_wide_kernel<G>), grid, dim3(kAttnWaves * 64), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_splits == 1) return e;
-  hipLaunchKernelGGL(attn_combine_kernel<G>, dim3((unsigned)(rows * G)), dim3(128), 0, stream, a);
+  hipLaunchKernelGGL(attn_combine_kernel<G>, dim3((unsigned)((rows * G + kCombineThreads / 64 - 1) / (kCombineThreads / 64))),
+                     dim3(kCombineThreads), 0, stream, a, rows * G);
   return hipGetLastError();
 }
 
@@ -667,7 +671,8 @@ static hipError_t launch_step_g(const SelectArgs& s, const AttnArgs& a, bool spl
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_splits == 1) return e;
-  hipLaunchKernelGGL(attn_combine_kernel<G>, dim3((unsigned)(rows * G)), dim3(128), 0, stream, a);
+  hipLaunchKernelGGL(attn_combine_kernel<G>, dim3((unsigned)((rows * G + kCombineThreads / 64 - 1) / (kCombineThreads / 64))),
+                     dim3(kCombineThreads), 0, stream, a, rows * G);
   return hipGetLastError();
 }
 

@@ -208,6 +208,138 @@ __device__ __forceinline__ void radix_topk_emit(const float* bs, int C, int n_ta
   }
 }
 
+// One wavefront's exact top-k over C <= 64 R keys (order-preserving score bits) in its registers:
+// candidate 64 i + lane is key i of the lane (0, below every score, past C).  0 < n < C; writes cand_lo +
+// the chosen candidates in ascending order to out[0 .. n).  list: 64 uint32 of LDS.  The n-th
+// largest key is bracketed by counts (a compare and a scalar bit count per 64 candidates): two
+// thresholds around a normal-model guess first, then one at a time by linear interpolation, every
+// third by bisection, until at most 64 keys are left between them; those are compacted into LDS, one
+// per lane, and ranked.  The emission walks the registers in index order; keys equal to the n-th go
+// to the lowest indices.  kScores: the scores themselves are roughly normal; otherwise (weights, all
+// positive and skewed) their keys, which grow with the logarithm.
+template <int R, bool kScores>
+__device__ __forceinline__ void reg_topk_emit(const uint32_t (&key)[R], int C, int n, int cand_lo, int16_t* out,
+                                              uint32_t* list) {
+  const int lane = threadIdx.x & 63;
+  uint32_t k_max = 0u, k_min = ~0u;
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    k_max = max(k_max, key[i]);
+    k_min = min(k_min, 64 * i + lane < C ? key[i] : ~0u);
+  }
+  k_max = row16_max(k_max);
+  k_min = row16_min(k_min);
+  k_max = max(k_max, (uint32_t)__shfl_xor((int)k_max, 16, kWave));
+  k_min = min(k_min, (uint32_t)__shfl_xor((int)k_min, 16, kWave));
+  k_max = __builtin_amdgcn_readfirstlane(max(k_max, (uint32_t)__shfl_xor((int)k_max, 32, kWave)));
+  k_min = __builtin_amdgcn_readfirstlane(min(k_min, (uint32_t)__shfl_xor((int)k_min, 32, kWave)));
+  auto above = [&](uint32_t t) {  // keys larger than t
+    int m = 0;
+#pragma unroll
+    for (int i = 0; i < R; ++i) m += (int)__popcll(__ballot(key[i] > t));
+    return m;
+  };
+  // count(> lo) = c_lo >= n, count(> hi) = c_hi < n throughout
+  uint32_t lo = k_min > 0u ? k_min - 1u : 0u, hi = k_max;
+  int c_lo = C, c_hi = 0;
+  auto cut = [&](uint32_t t) {
+    if (t <= lo || t >= hi) return;
+    const int m = above(t);
+    if (m >= n) {
+      lo = t;
+      c_lo = m;
+    } else {
+      hi = t;
+      c_hi = m;
+    }
+  };
+  {
+    // mean and deviation, and thresholds about 20 keys to either side of the guess
+    float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const float x = kScores ? key_value(key[i]) : (float)(key[i] - k_min);
+      if (64 * i + lane < C) {
+        s1 += x;
+        s2 = fmaf(x, x, s2);
+      }
+    }
+    s1 = row16_sum(s1);
+    s2 = row16_sum(s2);
+    s1 += __shfl_xor(s1, 16, kWave);
+    s2 += __shfl_xor(s2, 16, kWave);
+    s1 = readlane_f(s1 + __shfl_xor(s1, 32, kWave), 0);
+    s2 = readlane_f(s2 + __shfl_xor(s2, 32, kWave), 0);
+    const float mean = s1 / C, dev = __builtin_amdgcn_sqrtf(fmaxf(s2 / C - mean * mean, 0.f));
+    const float z = upper_normal_quantile((float)n / C);
+    const float step = 20.f * dev / (C * 0.3989f * __builtin_amdgcn_exp2f(-0.7213f * z * z));
+    auto key_at = [&](float x) {
+      if (kScores) return score_key(x);
+      return x > 0.f && x < 4e9f ? k_min + (uint32_t)x : 0u;
+    };
+    const float t0 = mean + z * dev;
+    if (t0 - t0 == 0.f && step - step == 0.f) {  // finite
+      cut(__builtin_amdgcn_readfirstlane(key_at(t0 - step)));
+      cut(__builtin_amdgcn_readfirstlane(key_at(t0 + step)));
+    }
+  }
+  for (int pass = 0;; ++pass) {  // every cut narrows (lo, hi)
+    if (c_lo - c_hi <= 64 || hi - lo <= 1u || c_lo == n) break;
+    const uint32_t span = hi - lo;
+    uint32_t t = lo + span / 2;
+    if (pass % 3 != 2) {
+      const float f = ((float)(c_lo - n) + 0.5f) / (float)(c_lo - c_hi);  // in (0, 1)
+      t = lo + min(max((uint32_t)(f * (float)span), 1u), span - 1u);
+    }
+    cut(t);
+  }
+  // T: keys above it are chosen, and the first `equal` keys equal to it
+  uint32_t T = lo;
+  int equal = 0;
+  if (c_lo != n) {
+    if (c_lo - c_hi <= 64) {  // rank the keys in (lo, hi]
+      int base = 0;
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const bool in = key[i] > lo && key[i] <= hi;
+        const uint64_t b = __ballot(in);
+        if (b != 0ull) {
+          if (in) list[base + mbcnt64(b)] = key[i];
+          base += (int)__popcll(b);
+        }
+      }
+      wave_lds_sync();
+      const uint32_t mine = lane < base ? list[lane] : 0u;
+      int more = 0, same = 0;
+      for (int j = 0; j < base; ++j) {
+        const uint32_t o = (uint32_t)readlane_i((int)mine, j);
+        more += o > mine;
+        same += o == mine;
+      }
+      const int want = n - c_hi - 1;  // the n-th largest key's rank in the list
+      const uint64_t hit = __ballot(lane < base && more <= want && want < more + same);
+      const int src = hit ? (int)__builtin_ctzll(hit) : 0;  // some lane holds it
+      T = (uint32_t)readlane_i((int)mine, src);
+      equal = n - c_hi - readlane_i(more, src);
+    } else {  // hi - lo == 1: more than 64 keys equal to hi
+      T = hi;
+      equal = n - c_hi;
+    }
+  }
+  int base = 0, ties = 0;
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const uint64_t eq = equal > ties ? __ballot(key[i] == T) : 0ull;
+    const uint64_t gt = __ballot(key[i] > T);
+    if ((eq | gt) == 0ull) continue;
+    const bool chosen = key[i] > T || (((eq >> lane) & 1ull) && ties + mbcnt64(eq) < equal);
+    const uint64_t b = __ballot(chosen);
+    if (chosen) out[base + mbcnt64(b)] = (int16_t)(cand_lo + 64 * i + lane);
+    base += (int)__popcll(b);
+    ties += (int)__popcll(eq);
+  }
+}
+
 // Bin of score s among 256 equal-width bins over [lo, lo + 256 / scale]: non-decreasing in s
 // (each step rounds monotonically), so a higher bin holds only larger scores.
 __device__ __forceinline__ int lin_bin(float s, float lo, float scale) {
@@ -225,7 +357,10 @@ __device__ __forceinline__ int lin_bin(float s, float lo, float scale) {
 // index), which gives the last chosen pair (kk, ki): a score is chosen when its key is above kk,
 // or equal to it at an index no higher than ki.  Thread t handles candidates 4 t .. 4 t + 3 of
 // each run of 4 kDecThreads, so thread order is candidate order and one flag prefix per run
-// places the chosen ones.  Four barriers for up to 2048 candidates.  Ranges that do not bin
+// places the chosen ones.  Four barriers for up to 2048 candidates; up to 64 candidates take one
+// wavefront and no barrier (18.3 to STEP_SMALL us for the whole decode step at 4K, batch 1; the register
+// form above on one wavefront was slower than the workgroup at 512 candidates: 44.3 us against 42.3
+// for the step at 32K, batch 8).  Ranges that do not bin
 // (non-finite or equal extremes) and threshold bins of more than kTopkList scores take the
 // radix form.
 // LDS use: hist[0 .. 256) histogram, [256 .. 272) wavefront extremes, then the emission's
@@ -264,6 +399,20 @@ __device__ __forceinline__ void block_topk_emit(const float* bs, int C, int n_ta
   uint32_t* ext = hist + 256;
   uint32_t* list = hist + 272;
   uint32_t* list_n = hist + 400;
+  if (C <= kWave) {  // every score in a lane of one wavefront, ranked there; no barrier
+    if (wave == 0) {
+      const uint32_t mine = lane < C ? score_key(bs[lane]) : 0u;
+      int rank = 0;  // keys that come first: larger, or equal at a lower index
+      for (int j = 0; j < C; ++j) {
+        const uint32_t o = (uint32_t)readlane_i((int)mine, j);
+        rank += (o > mine || (o == mine && j < lane)) ? 1 : 0;
+      }
+      const bool chosen = lane < C && rank < n_take;
+      const uint64_t cb = __ballot(chosen);
+      if (chosen) chosen_out[mbcnt64(cb)] = (int16_t)(cand_lo + lane);
+    }
+    return;
+  }
   uint32_t kmin = 0xffffffffu, kmax = 0u;
   if (!prepared) {  // extremes of the keys
     for (int c0 = 0; c0 < C; c0 += kRun) {
