@@ -358,7 +358,7 @@ __device__ __forceinline__ int lin_bin(float s, float lo, float scale) {
 // or equal to it at an index no higher than ki.  Thread t handles candidates 4 t .. 4 t + 3 of
 // each run of 4 kDecThreads, so thread order is candidate order and one flag prefix per run
 // places the chosen ones.  Four barriers for up to 2048 candidates; up to 64 candidates take one
-// wavefront and no barrier (18.3 to STEP_SMALL us for the whole decode step at 4K, batch 1; the register
+// wavefront and no barrier (18.3 to 17.9 us for the whole decode step at 4K, batch 1; the register
 // form above on one wavefront was slower than the workgroup at 512 candidates: 44.3 us against 42.3
 // for the step at 32K, batch 8).  Ranges that do not bin
 // (non-finite or equal extremes) and threshold bins of more than kTopkList scores take the
