@@ -95,6 +95,28 @@ __device__ __forceinline__ float block_sum_f(float x, float* red, int wave, int 
   return s;
 }
 
+// Three sums over the workgroup in one round of barriers.  red: at least 3 * kDecThreads / 64 floats.
+__device__ __forceinline__ void block_sum3_f(float (&x)[3], float* red, int wave, int lane) {
+  constexpr int kWaves = kDecThreads / 64;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    x[i] = row16_sum(x[i]);
+    x[i] += __shfl_xor(x[i], 16, kWave);
+    x[i] += __shfl_xor(x[i], 32, kWave);
+  }
+  __syncthreads();
+  if (lane == 0)
+#pragma unroll
+    for (int i = 0; i < 3; ++i) red[i * kWaves + wave] = x[i];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    x[i] = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) x[i] += red[i * kWaves + w];
+  }
+}
+
 __device__ __forceinline__ float block_max_f(float x, float* red, int wave, int lane) {
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) x = fmaxf(x, __shfl_xor(x, d, kWave));
@@ -147,7 +169,7 @@ __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
   __shared__ __align__(16) uint32_t hist[kTopkLds];
   __shared__ int wave_cnt[kDecThreads / 64];
   __shared__ int pick[3];
-  __shared__ float red[kDecThreads / 64];
+  __shared__ float red[3 * (kDecThreads / 64)];
   __shared__ float red_m[kDecThreads / 64][16], red_s[kDecThreads / 64][16];
   const int64_t row = blockIdx.x;  // (b * Hkv + m) * n_q + r
   const int r = (int)(row % a.n_q);
@@ -158,11 +180,7 @@ __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
   const int64_t p = a.q_pos0 + r;
   const int N = grid_win_vis(a.grid, p) + 1;           // positions 0 .. N - 1 (host-checked)
   const int n_tw = (int)p;                              // fine windows 0 .. p - 1 are complete at p
-  for (int w = tid; w < N; w += kDecThreads) {
-    Tp[w] = 0.f;
-    chosen[w] = 0;
-  }
-  __syncthreads();
+  float zl = -INFINITY;  // the largest logit of the thread's positions
 
   // ---- target
   if (kPre) {
@@ -170,13 +188,23 @@ __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
     // within [w s, w s + l), i.e. i in [w s, w s + l - 2]: l / 16 segments of 16 fine windows, the last
     // one without its last window; every position complete at p has them
     const float2* seg = reinterpret_cast<const float2*>(a.sw + row * a.sw_stride);
+    const float* z = a.z + row * a.sw_stride;  // the row's logits, from kl_predict_kernel
     const int gs = a.grid.s / 16, gl = a.grid.l / 16;
     for (int w = tid; w < N; w += kDecThreads) {
+      const float zw = z[w];
       float m = seg[w * gs + gl - 1].x;
       for (int i = 0; i < gl - 1; ++i) m = fmaxf(m, seg[w * gs + i].y);
       Tp[w] = m;
+      Pp[w] = zw;
+      zl = fmaxf(zl, zw);
+      chosen[w] = 0;
     }
   } else {  // MFMA tiles of 16 fine windows x the group's heads
+    for (int w = tid; w < N; w += kDecThreads) {
+      Tp[w] = 0.f;
+      chosen[w] = 0;
+    }
+    __syncthreads();
     bf16x8 qb[4];
     // columns past the group's heads read head 0 (a valid address) and are zeroed
     const uint16_t* qrow = a.q + ((bm * G + (n < G ? n : 0)) * a.n_q + r) * kHeadDim + 8 * j;
@@ -246,12 +274,10 @@ __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
   }
   __syncthreads();
 
-  // ---- prediction: the row's logits, from kl_predict_kernel or a Forecast GEMV over the positions (16
-  // lanes per position), then its softmax
-  if (kPre) {
-    const float* z = a.z + row * a.sw_stride;
-    for (int w = tid; w < N; w += kDecThreads) Pp[w] = z[w];
-  } else {
+  // ---- prediction: the logits, from kl_predict_kernel (above) or a Forecast GEMV over the positions (16
+  // lanes per position), then their softmax.  A position's entries are read and written by its own
+  // thread from here to the top-k, and between the top-k and the gradient.
+  if (!kPre) {
     const int c = lane & 15, rs = lane >> 4;
     float fv[8];
     {
@@ -277,9 +303,10 @@ __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
       if (c == 0 && w < N) Pp[w] = d;
     }
   }
-  __syncthreads();
-  float zl = -INFINITY;
-  for (int w = tid; w < N; w += kDecThreads) zl = fmaxf(zl, Pp[w]);
+  if (!kPre) {
+    __syncthreads();
+    for (int w = tid; w < N; w += kDecThreads) zl = fmaxf(zl, Pp[w]);
+  }
   const float zmax = block_max_f(zl, red, wave, lane);
   float el = 0.f;
   for (int w = tid; w < N; w += kDecThreads) {
@@ -288,7 +315,6 @@ __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
     el += e;
   }
   const float pinv = 1.0f / block_sum_f(el, red, wave, lane);
-  for (int w = tid; w < N; w += kDecThreads) Pp[w] *= pinv;
 
   // ---- the target's top-k among positions inside candidate blocks [n_init, blk(p) - n_local]
   const int blk = (int)(p / kBlock);
@@ -308,52 +334,67 @@ __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
   __syncthreads();
 
   // ---- buckets and loss
-  float tt = 0.f, tr = 0.f, pr = 0.f;
+  float sums[3] = {0.f, 0.f, 0.f};  // the target, then target and prediction outside the chosen positions
   for (int w = tid; w < N; w += kDecThreads) {
-    tt += Tp[w];
+    const float t = Tp[w], pw = Pp[w] * pinv;
+    Pp[w] = pw;
+    sums[0] += t;
     if (!chosen[w]) {
-      tr += Tp[w];
-      pr += Pp[w];
+      sums[1] += t;
+      sums[2] += pw;
     }
   }
-  const float Ttot = block_sum_f(tt, red, wave, lane);
-  const float Trest = block_sum_f(tr, red, wave, lane);
-  const float R = block_sum_f(pr, red, wave, lane);
+  block_sum3_f(sums, red, wave, lane);
+  const float Ttot = sums[0], R = sums[2];
   const float tinv = 1.0f / Ttot;
-  const float t_rest = Trest / Ttot;
+  const float t_rest = sums[1] / Ttot;
+  const float rest_f = R > 0.f ? 1.0f - t_rest / R : 0.f;
   float kl = 0.f;
   for (int w = tid; w < N; w += kDecThreads) {
+    const float pw = Pp[w];
     if (chosen[w]) {
       const float tc = Tp[w] * tinv;
-      if (tc > 0.f) kl += tc * __logf(tc / Pp[w]);
+      if (tc > 0.f) kl += tc * __logf(tc / pw);
+      Pp[w] = pw - tc;
+    } else {
+      Pp[w] = pw * rest_f;
     }
   }
-  kl = block_sum_f(kl, red, wave, lane);
+  kl = block_sum_f(kl, red, wave, lane);  // its barriers also make every position's weight visible
   if (tid == 0) a.loss[row] = kl + (t_rest > 0.f ? t_rest * __logf(t_rest / R) : 0.f);
 
   // ---- gradient: dF[d] = sm_scale sum_w g_w K~p_w[d].  The weights g replace P in LDS; lane l of
   // wavefront v takes dimensions 8 (l % 16) .. + 7 of positions 4 (v + 8 i) + l / 16, so a wavefront
   // load is 1 KiB of K~p and a position's weight one LDS read for 16 lanes (a 2-byte load, two LDS reads
   // and a flag per product before: 270 of the 785 us of the kernel at 2048 rows of 4094 positions).
-  const float rest_f = R > 0.f ? 1.0f - t_rest / R : 0.f;
-  for (int w = tid; w < N; w += kDecThreads) Pp[w] = chosen[w] ? Pp[w] - Tp[w] * tinv : Pp[w] * rest_f;
-  __syncthreads();
+  // What bounds the kernel is latency, four rows to a CU: eight loads are in flight per wavefront here,
+  // and each pass over the positions above does all it can for its barrier (208 to 135 us; one load at a
+  // time 208, four 138).
   {
+    constexpr int kStep = (kDecThreads / 64) * 4, kBatch = 8;
     const int c = lane & 15, rs = lane >> 4;
     const uint16_t* kpb = a.kp + bm * a.nc_cap * kHeadDim + 8 * c;
     float acc[8] = {};
-    for (int base = wave * 4; base < N; base += (kDecThreads / 64) * 4) {
-      const int w = base + rs;
-      const uint4 k = ld16(kpb + (int64_t)min(w, N - 1) * kHeadDim);
-      const float g = w < N ? Pp[w] : 0.f;
-      acc[0] = fmaf(g, bf16lo(k.x), acc[0]);
-      acc[1] = fmaf(g, bf16hi(k.x), acc[1]);
-      acc[2] = fmaf(g, bf16lo(k.y), acc[2]);
-      acc[3] = fmaf(g, bf16hi(k.y), acc[3]);
-      acc[4] = fmaf(g, bf16lo(k.z), acc[4]);
-      acc[5] = fmaf(g, bf16hi(k.z), acc[5]);
-      acc[6] = fmaf(g, bf16lo(k.w), acc[6]);
-      acc[7] = fmaf(g, bf16hi(k.w), acc[7]);
+    for (int base = wave * 4; base < N; base += kBatch * kStep) {
+      uint4 k[kBatch];
+      float g[kBatch];
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int w = base + i * kStep + rs, wc = min(w, N - 1);
+        k[i] = ld16(kpb + (int64_t)wc * kHeadDim);
+        g[i] = w < N ? Pp[wc] : 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        acc[0] = fmaf(g[i], bf16lo(k[i].x), acc[0]);
+        acc[1] = fmaf(g[i], bf16hi(k[i].x), acc[1]);
+        acc[2] = fmaf(g[i], bf16lo(k[i].y), acc[2]);
+        acc[3] = fmaf(g[i], bf16hi(k[i].y), acc[3]);
+        acc[4] = fmaf(g[i], bf16lo(k[i].z), acc[4]);
+        acc[5] = fmaf(g[i], bf16hi(k[i].z), acc[5]);
+        acc[6] = fmaf(g[i], bf16lo(k[i].w), acc[6]);
+        acc[7] = fmaf(g[i], bf16hi(k[i].w), acc[7]);
+      }
     }
     // the wavefront's four position residues, then the wavefronts through LDS (the target scores are no
     // longer needed: at least 512 floats, so two rounds of four wavefronts)
