@@ -28,7 +28,10 @@ namespace sparda {
 
 // grid.x = row * n_chunks + chunk; a chunk is 256 windows (64 per wavefront).  Lane l reads dims
 // 8*(l%16)..+7 of window 4 i + l/16: each wavefront load is 1 KiB contiguous of K~.  Window
-// first + x of the row goes to scratch slot x.
+// first + x of the row goes to scratch slot x.  kOnce (one row per (batch, group)): no other row
+// reads the keys, so they are streamed past the caches (decode step of 64 rows at 128K: 77.6 to
+// 74.9 us); rows of one group share them through L2 and load them the ordinary way.
+template <bool kOnce>
 __global__ __launch_bounds__(256) void rowwise_score_kernel(SelectArgs a, int n_chunks) {
   const int64_t row = blockIdx.x / n_chunks;
   const int chunk = (int)(blockIdx.x % n_chunks);
@@ -52,7 +55,7 @@ __global__ __launch_bounds__(256) void rowwise_score_kernel(SelectArgs a, int n_
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int idx = min(first + 4 * i + rs, nw - 1);  // past the last window: a repeat, never stored
-    kw[i] = ld16(kbase + (int64_t)idx * kHeadDim);
+    kw[i] = kOnce ? ld16_nt(kbase + (int64_t)idx * kHeadDim) : ld16(kbase + (int64_t)idx * kHeadDim);
   }
   float* out = a.ws + row * a.ws_stride;
 #pragma unroll
@@ -71,6 +74,14 @@ __global__ __launch_bounds__(256) void rowwise_score_kernel(SelectArgs a, int n_
   }
 }
 
+static hipError_t launch_rowwise_scores(const SelectArgs& a, int64_t rows, int n_chunks, hipStream_t stream) {
+  const dim3 grid((unsigned)(rows * n_chunks)), block(256);
+  if (a.n_q == 1)
+    hipLaunchKernelGGL(rowwise_score_kernel<true>, grid, block, 0, stream, a, n_chunks);
+  else
+    hipLaunchKernelGGL(rowwise_score_kernel<false>, grid, block, 0, stream, a, n_chunks);
+  return hipGetLastError();
+}
 
 // Rows with at most this many candidates keep their block keys in registers (row_topk_kernel); longer
 // rows run the radix passes over the workspace (rowwise_topk_kernel).
@@ -131,12 +142,27 @@ __global__ __launch_bounds__(256) void row_topk_kernel(SelectArgs a, int64_t n_r
   int32_t wf, wl;
   row_windows(g, a.grid, p, &wf, &wl);
   const int32_t wvis = grid_win_vis(a.grid, p);
-  uint32_t key[R];
+  uint32_t key[R];  // slots past the row's candidates: key 0, below every score
+  // A block's windows on a grid that divides the block are 64 / s - 1 + l / s.  Up to five of them
+  // ((32, 16) has five) are loaded without a loop, repeats past the last one: every slot's loads are
+  // then requested before the first is waited for.
+  if (!kPooled && kBlock % a.grid.s == 0 && a.grid.l % a.grid.s == 0 && kBlock / a.grid.s + a.grid.l / a.grid.s <= 6) {
 #pragma unroll
-  for (int i = 0; i < R; ++i) {  // slots past the row's candidates: key 0, below every score
-    const int c = 64 * i + lane;
-    const float x = candidate_score<kPooled>(a, sc, g.cand_lo, min(c, C - 1), wf, wvis);
-    key[i] = c < C ? score_key(x) : 0u;
+    for (int i = 0; i < R; ++i) {
+      const int c = 64 * i + lane, j = g.cand_lo + min(c, C - 1);
+      const int lo = grid_win_lo(a.grid, j), hi = max(lo, min(grid_win_hi(a.grid, j), wvis));
+      float x = sc[lo - wf];
+#pragma unroll
+      for (int u = 1; u < 5; ++u) x = fmaxf(x, sc[min(lo + u, hi) - wf]);
+      key[i] = c < C ? score_key(x) : 0u;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int c = 64 * i + lane;
+      const float x = candidate_score<kPooled>(a, sc, g.cand_lo, min(c, C - 1), wf, wvis);
+      key[i] = c < C ? score_key(x) : 0u;
+    }
   }
   reg_topk_emit<R, kPooled>(key, C, n, g.cand_lo, out, list[wave]);
 }
@@ -240,8 +266,7 @@ hipError_t launch_decode_split_scores(const SelectArgs& a, hipStream_t stream) {
   row_windows(g, a.grid, a.q_pos0, &wf, &wl);
   if (g.n_cand <= 0 || wl < wf) return hipSuccess;
   const int n_chunks = (wl - wf + 1 + 255) / 256;
-  hipLaunchKernelGGL(rowwise_score_kernel, dim3((unsigned)(rows * n_chunks)), dim3(256), 0, stream, a, n_chunks);
-  return hipGetLastError();
+  return launch_rowwise_scores(a, rows, n_chunks, stream);
 }
 
 bool select_needs_scratch(int64_t rows, int32_t n_q, int64_t q_pos0, int32_t n_init, int32_t n_local, WinGrid grid) {
@@ -269,8 +294,7 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
     return e != hipSuccess ? e : launch_topk<true>(a, stream);
   } else if (gl.n_cand > 0 && wl >= wf) {  // the last row scores the most windows
     const int n_chunks = (wl - wf + 1 + 255) / 256;
-    hipLaunchKernelGGL(rowwise_score_kernel, dim3((unsigned)(rows * n_chunks)), dim3(256), 0, stream, a, n_chunks);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_rowwise_scores(a, rows, n_chunks, stream);
     if (e != hipSuccess) return e;
   }
   if (path != kPathDecodeSplit) return launch_topk<false>(a, stream);
