@@ -49,7 +49,7 @@ struct AttnLds {
 // Attention of query row `row`, split `split` of its block list, by a workgroup of NW
 // wavefronts (every thread must call it).  srow: the row's a.k_total entries (global or LDS),
 // n_listed: its count.
-template <int G, int NW>
+template <int G, int NW, bool kOnce>
 __device__ __forceinline__ void attend_row(const AttnArgs& a, int64_t row, int split, AttnLds<G, NW>& L,
                                            const int16_t* srow, int n_listed) {
   auto& kst = L.kst;
@@ -118,11 +118,11 @@ __device__ __forceinline__ void attend_row(const AttnArgs& a, int64_t row, int s
   auto load_k = [&](int64_t base, int lo, int hi) {
 #pragma unroll
     for (int it = 0; it < 16; ++it)
-      if (it >= lo && it < hi) kw[it] = ld16_nt(a.k + base + (4 * it + grp) * kHeadDim + 8 * hh);
+      if (it >= lo && it < hi) kw[it] = ld16_hint<kOnce>(a.k + base + (4 * it + grp) * kHeadDim + 8 * hh);
   };
   auto load_v = [&](int64_t base) {
 #pragma unroll
-    for (int it = 0; it < 16; ++it) vw[it] = ld16_nt(a.v + base + (4 * it + grp) * kHeadDim + 8 * hh);
+    for (int it = 0; it < 16; ++it) vw[it] = ld16_hint<kOnce>(a.v + base + (4 * it + grp) * kHeadDim + 8 * hh);
   };
   uint16_t* ks_w = &kst[wave][0];
   // Software pipeline over the wavefront's blocks: the first half of the next block's K is
@@ -262,11 +262,11 @@ __device__ __forceinline__ void attend_row(const AttnArgs& a, int64_t row, int s
   }
 }
 
-template <int G, int NW>
+template <int G, int NW, bool kOnce>
 __global__ __launch_bounds__(NW * 64) void sparse_attn_kernel(AttnArgs a) {
   __shared__ __align__(16) AttnLds<G, NW> lds;
   const int64_t row = blockIdx.x;
-  attend_row<G, NW>(a, row, blockIdx.y, lds, a.sel + row * a.k_total, a.cnt[row]);
+  attend_row<G, NW, kOnce>(a, row, blockIdx.y, lds, a.sel + row * a.k_total, a.cnt[row]);
 }
 
 // One decode step of a (batch, group) row: the row's Forecast selection (Sec. 4.1, Eq. 4 with
@@ -286,7 +286,7 @@ __device__ __forceinline__ void step_select(const SelectArgs& s, int64_t row, fl
   if constexpr (kSplitSel)
     decode_topk_row(s, row, sc, hist, wave_cnt, pick, set, set_cnt);
   else
-    decode_select_row(s, row, sc, hist, wave_cnt, pick, set, set_cnt);
+    decode_select_row<true>(s, row, sc, hist, wave_cnt, pick, set, set_cnt);
   __syncthreads();  // the row's set is in LDS, and the selection's LDS is free
   if (blockIdx.y == 0) {
     for (int i = threadIdx.x; i < s.k_total; i += kDecThreads) s.sel[row * s.k_total + i] = set[i];
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(NW * 64) void decode_step_kernel(SelectArgs s, Attn
   const int64_t row = blockIdx.x;
   step_select<kSplitSel>(s, row, reinterpret_cast<float*>(&lds.kst[0][0]), reinterpret_cast<uint32_t*>(&lds.p_lds[0][0][0]),
                          wave_cnt, pick, set, &set_cnt);
-  attend_row<G, NW>(a, row, blockIdx.y, lds, set, set_cnt);
+  attend_row<G, NW, true>(a, row, blockIdx.y, lds, set, set_cnt);
 }
 
 // Decode attention for groups of 6 to 16 heads: P V on MFMA.  With this many query rows per
@@ -341,7 +341,7 @@ struct WideLds {
 
 // The wide kernel's attention of query row `row`, split `split`, over srow (a.k_total entries,
 // global or LDS) with n_listed of them valid.  Every thread of the workgroup must call it.
-template <int G>
+template <int G, bool kOnce>
 __device__ __forceinline__ void attend_row_wide(const AttnArgs& a, int64_t row, int split, WideLds& L,
                                                 const int16_t* srow, int n_listed) {
   constexpr int NW = kAttnWaves;
@@ -394,12 +394,12 @@ __device__ __forceinline__ void attend_row_wide(const AttnArgs& a, int64_t row, 
   auto issue_k = [&](int s, int j, int hf) {
     const char* src = half_at(a.k, s, j, hf);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) lds_load16(src + 1024 * i, k_off ^ ((i & 3) << 6), k_at + 1024 * i);
+    for (int i = 0; i < 8; ++i) lds_load16<kOnce>(src + 1024 * i, k_off ^ ((i & 3) << 6), k_at + 1024 * i);
   };
   auto issue_v = [&](int s, int j, int hf) {
     const char* src = half_at(a.v, s, j, hf);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) lds_load16(src + 1024 * i, v_off ^ ((i & 1) << 7), v_at + 1024 * i);
+    for (int i = 0; i < 8; ++i) lds_load16<kOnce>(src + 1024 * i, v_off ^ ((i & 1) << 7), v_at + 1024 * i);
   };
 
   int j = 0, hf = 0;
@@ -545,11 +545,11 @@ __device__ __forceinline__ void attend_row_wide(const AttnArgs& a, int64_t row, 
   }
 }
 
-template <int G>
+template <int G, bool kOnce>
 __global__ __launch_bounds__(kAttnWaves * 64) void sparse_attn_wide_kernel(AttnArgs a) {
   __shared__ __align__(16) WideLds lds;
   const int64_t row = blockIdx.x;
-  attend_row_wide<G>(a, row, blockIdx.y, lds, a.sel + row * a.k_total, a.cnt[row]);
+  attend_row_wide<G, kOnce>(a, row, blockIdx.y, lds, a.sel + row * a.k_total, a.cnt[row]);
 }
 
 // The decode step with the wide kernel's attention (6 <= G <= 16): as decode_step_kernel.
@@ -565,7 +565,7 @@ __global__ __launch_bounds__(kAttnWaves * 64) void decode_step_wide_kernel(Selec
   __shared__ int16_t set_cnt;
   const int64_t row = blockIdx.x;
   step_select<kSplitSel>(s, row, reinterpret_cast<float*>(&lds.kv[0][0][0]), hist, wave_cnt, pick, set, &set_cnt);
-  attend_row_wide<G>(a, row, blockIdx.y, lds, set, set_cnt);
+  attend_row_wide<G, true>(a, row, blockIdx.y, lds, set, set_cnt);
 }
 
 // Merge the split partials of one (row, head) by log-sum-exp: one wavefront, two head dims per lane.
@@ -643,10 +643,23 @@ static hipError_t launch_g(const AttnArgs& a, hipStream_t stream) {
   // Up to 5 heads: P V on the VALU.  6 to 16 heads: P V on MFMA (sparse_attn_wide_kernel; at 6
   // heads the VALU kernel's accumulators no longer fit beside a block's K and V without spills).
   dim3 grid((unsigned)rows, (unsigned)a.n_splits);
-  if constexpr (G <= 5)
-    hipLaunchKernelGGL((sparse_attn_kernel<G, kAttnWaves>), grid, dim3(kAttnWaves * 64), 0, stream, a);
-  else
-    hipLaunchKernelGGL((sparse_attn_wide_kernel<G>), grid, dim3(kAttnWaves * 64), 0, stream, a);
+  const dim3 block(kAttnWaves * 64);
+  // One row per group reads its blocks once: they bypass the caches (decode step of 64 rows at 128K,
+  // 16 heads: 74.1 to 70.4 us).  Several rows of a group list many of the same blocks and take them
+  // from L2: 5 rows x 64 groups of 4 heads at 32K 97.1 us, with the hint 109.8; 5 x 16 of 7 heads 32.5
+  // against 36.4; 512 x 4 of 3 heads 269.9 against 332.8.
+  const bool once = a.n_q == 1;
+  if constexpr (G <= 5) {
+    if (once)
+      hipLaunchKernelGGL((sparse_attn_kernel<G, kAttnWaves, true>), grid, block, 0, stream, a);
+    else
+      hipLaunchKernelGGL((sparse_attn_kernel<G, kAttnWaves, false>), grid, block, 0, stream, a);
+  } else {
+    if (once)
+      hipLaunchKernelGGL((sparse_attn_wide_kernel<G, true>), grid, block, 0, stream, a);
+    else
+      hipLaunchKernelGGL((sparse_attn_wide_kernel<G, false>), grid, block, 0, stream, a);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_splits == 1) return e;
   hipLaunchKernelGGL(attn_combine_kernel<G>, dim3((unsigned)((rows * G + kCombineThreads / 64 - 1) / (kCombineThreads / 64))),

@@ -212,17 +212,29 @@ __device__ __forceinline__ uint4 ld16_nt(const void* p) {
   const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
+template <bool kNt>
+__device__ __forceinline__ uint4 ld16_hint(const void* p) {
+  if constexpr (kNt) return ld16_nt(p);
+  return ld16(p);
+}
 
 // 16 bytes per lane from global memory (uniform base + the lane's 32-bit offset) straight into LDS:
 // lane l's piece lands at byte address dst + 16 l of the workgroup's LDS (dst wavefront-uniform).
 // Written as one instruction because the builtin makes the compiler wait for every such load in
 // flight before any later LDS read; the instruction has no output register, and the caller waits
-// for it (vmcnt) before the barrier that hands the rows over.
+// for it (vmcnt) before the barrier that hands the rows over.  kNt: with the non-temporal hint.
+template <bool kNt = false>
 __device__ __forceinline__ void lds_load16(const void* base, uint32_t off, uint32_t dst) {
-  __asm__ __volatile__("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                       :
-                       : "v"(off), "s"(base), "s"(dst)
-                       : "memory");
+  if constexpr (kNt)
+    __asm__ __volatile__("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
+                         :
+                         : "v"(off), "s"(base), "s"(dst)
+                         : "memory");
+  else
+    __asm__ __volatile__("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                         :
+                         : "v"(off), "s"(base), "s"(dst)
+                         : "memory");
 }
 // Waits for every such load (and every other memory access) of the wavefront.
 __device__ __forceinline__ void lds_loads_landed() {

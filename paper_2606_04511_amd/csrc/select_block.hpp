@@ -554,6 +554,7 @@ __device__ __forceinline__ void block_topk_emit(const float* bs, int C, int n_ta
 // (kDecThreads / 64 ints) and pick (3 ints) are LDS.  The row's set (a.k_total entries) goes to
 // out and its count to *cnt_out (global or LDS), complete once every thread has returned and
 // synchronised.
+template <bool kOnce>
 __device__ __forceinline__ void decode_select_row(const SelectArgs& a, int64_t row, float* sc, uint32_t* hist,
                                                   int* wave_cnt, int* pick, int16_t* out, int16_t* cnt_out) {
 
@@ -591,7 +592,7 @@ __device__ __forceinline__ void decode_select_row(const SelectArgs& a, int64_t r
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int idx = min(base + 4 * i + rs, NW - 1);
-        w[i] = ld16_nt(kbase + (int64_t)idx * kHeadDim);
+        w[i] = ld16_hint<kOnce>(kbase + (int64_t)idx * kHeadDim);
       }
     };
     int base = wave * 64;
