@@ -270,7 +270,11 @@ hipError_t launch_decode_split_scores(const SelectArgs& a, hipStream_t stream) {
   return launch_rowwise_scores(a, rows, n_chunks, stream);
 }
 
+// The workspace that a call must bring depends on its rows' lengths alone: a call of few rows past the
+// tile kernel's candidates needs the row-wise path's, though the decode kernel leaves it unused.
 bool select_needs_scratch(int64_t rows, int32_t n_q, int64_t q_pos0, int32_t n_init, int32_t n_local, WinGrid grid) {
+  if (n_q > 1)
+    return !tile_grid(grid) || row_geom(q_pos0 + n_q - 1, n_init, n_local, 1 << 30).n_cand > kSelTileMaxCand;
   const SelectPath path = select_path(rows, n_q, q_pos0, n_init, n_local, grid);
   return path == kPathRowwise || path == kPathDecodeSplit;
 }
