@@ -177,3 +177,53 @@ def test_few_rows_select(dev, B, H, n_q, T, grid):
     n, swaps = compare_selection(o, inputs.to_u16(f), inputs.to_u16(kc), n_q, q_pos0, sel.cpu().numpy(), cnt.cpu().numpy(),
                                  rows)
     say(f"  rows {n}, tie swaps {swaps}")
+
+
+# The combine reads 8 splits at a time: 8, 9 and 16 splits, and the most (64), with splits that hold no
+# block; heads that do and do not fill a workgroup of four; several rows of a group (its blocks' loads
+# then go through the caches).
+@pytest.mark.parametrize("G,n_q,T,k", [(4, 1, 9000, 64), (5, 1, 9000, 72), (16, 1, 9000, 128), (3, 3, 2100, 200),
+                                       (7, 2, 36000, 512), (1, 1, 36000, 512), (16, 1, 60, 128)])
+def test_attention_split_counts(dev, G, n_q, T, k):
+    say(f"attention splits G{G} n_q{n_q} T{T} k{k}")
+    H, q_pos0, t_cap = 1, T - n_q, -(-T // 64) * 64
+    s, o = shapes(1, H, G, k, t_cap, t_cap // 64, n_init=0, n_local=1)
+    sel, cnt = random_sets(np.random.default_rng(k + G), H, n_q, q_pos0, k)
+    kc = inputs.normal_bf16((1, H, t_cap, 128), 6, 0)
+    v = inputs.normal_bf16((1, H, t_cap, 128), 6, 1)
+    q = inputs.normal_bf16((1, H * G, n_q, 128), 6, 2)
+    ws = torch.empty(sp.sparda_workspace_size(s, sp.SPARDA_OP_SPARSE_ATTN, n_q, q_pos0), dtype=torch.uint8, device=dev)
+    out = torch.full((1, H * G, n_q, 128), math.nan, dtype=torch.bfloat16, device=dev)
+    sp.sparda_sparse_attn(s, q.to(dev), n_q, q_pos0, kc.to(dev), v.to(dev), 0, torch.from_numpy(sel).to(dev),
+                          torch.from_numpy(cnt).to(dev), SCALE, out, ws)
+    torch.cuda.synchronize()
+    q16, k16, v16 = inputs.to_u16(q), inputs.to_u16(kc), inputs.to_u16(v)
+    ref = oracle.sparse_attn(o, q16, n_q, q_pos0, k16, v16, 0, sel, cnt, SCALE)
+    wab = oracle.sparse_attn(o, q16, n_q, q_pos0, k16, abs_bits(v16), 0, sel, cnt, SCALE)
+    compare_attention(out.float().cpu().numpy(), ref, "splits", wab)
+
+
+# Decode selection of 63 to 65 candidates (one wavefront up to 64), ties included.
+@pytest.mark.parametrize("C", [2, 63, 64, 65])
+@pytest.mark.parametrize("levels", [0, 2])
+def test_decode_select_one_wavefront(dev, C, levels):
+    say(f"decode select C{C} levels {levels}")
+    H, k, T = 3, min(C + 2, 20), 64 * (C + 3)  # one initial and two local blocks beside C candidates
+    s, o = shapes(1, H, 4, k, T, C + 3)
+    f = inputs.normal_bf16((1, H, 1, 128), 9, 0)
+    kc = inputs.normal_bf16((1, H, C + 3, 128), 9, 1)
+    if levels:  # equal and few distinct scores
+        f.zero_()
+        f[..., 0] = 1.0
+        kc[..., 0] = torch.from_numpy(np.random.default_rng(C).integers(0, levels, size=(1, H, C + 3)).astype(np.float32)).to(kc.dtype)
+    sel = torch.full((1, H, 1, k), 777, dtype=torch.int16, device=dev)
+    cnt = torch.full((1, H, 1), 777, dtype=torch.int16, device=dev)
+    sp.sparda_forecast_select(s, f.to(dev), 1, T - 1, kc.to(dev), sel, cnt, torch.empty(16, dtype=torch.uint8, device=dev))
+    torch.cuda.synchronize()
+    sel, cnt = sel.cpu().numpy(), cnt.cpu().numpy()
+    f16, kc16 = inputs.to_u16(f), inputs.to_u16(kc)
+    if levels:
+        ref, rcnt = oracle.forecast_select(o, f16, 1, T - 1, kc16)
+        assert np.array_equal(cnt, rcnt) and np.array_equal(sel, ref)
+    else:
+        compare_selection(o, f16, kc16, 1, T - 1, sel, cnt, [(0, m, 0) for m in range(H)])
