@@ -270,7 +270,8 @@ int sparda_sparse_attn_noalloc(const sparda_shape* shape, const void* q, int32_t
  *   loss  out : float [B][Hkv][n_q] device.
  *   d_f   out : float [B][Hkv][n_q][D] device, d loss / d F.
  *   ws, ws_bytes: device workspace of sparda_workspace_size(SPARDA_OP_INDEXER_KL) bytes (the fine
- *               windows, then every row's target weight of each fine window).
+ *               windows, then for every row its target weights' maxima over segments of 16 fine
+ *               windows and its prediction logits).  d_f serves as scratch before it is written.
  * Per row at position p: positions w = the prediction windows complete at p; the target T_w =
  * max over the fine windows inside w (tokens [i, i + 2) within [w s, w s + l)) of the sum over the
  * group's heads of softmax_i(sm_scale q_h . K~fine_i) (fine windows complete at p); the

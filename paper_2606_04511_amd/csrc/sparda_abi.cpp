@@ -108,7 +108,8 @@ size_t multihead_ws(const sparda_shape* s, int32_t n_q, int64_t q_pos0, int64_t*
 }
 
 // Workspace of sparda_indexer_kl: the fine (2, 1) windows complete at the last row (bf16), then
-// every row's target weight of each of them (float, rows padded to 4).
+// one float per fine window and row (rows padded to 4): the row's segment maxima of the target weights
+// and its logits, or (group sizes without head tiles) unused.
 size_t kl_keys_bytes(const sparda_shape* s, int32_t n_q, int64_t q_pos0) {
   const int64_t nt = q_pos0 + n_q - 1;
   return (size_t)s->batch * s->n_kv_heads * (size_t)(nt > 0 ? nt : 1) * s->head_dim * sizeof(uint16_t);
