@@ -107,13 +107,14 @@ __host__ __device__ inline void row_windows(const RowGeom& g, const WinGrid& w, 
   *last = g.n_cand > 0 ? (hi < vis ? hi : vis) : *first - 1;
 }
 
-// True when the call keeps its window scores in workspace scratch: the row-wise path, and decode
-// calls with fewer rows than CUs (scored by many workgroups per row).
+// True when the call must bring workspace scratch for its scores: rows of multi-row calls past the
+// tile kernel's candidates, decode rows past the LDS, and decode calls with fewer rows than CUs
+// (scored by many workgroups per row).
 bool select_needs_scratch(int64_t rows, int32_t n_q, int64_t q_pos0, int32_t n_init, int32_t n_local, WinGrid grid);
 hipError_t launch_select(const SelectArgs& a, hipStream_t stream);
 // Which decode path a select call takes: 0 the fused kernel (one workgroup per row, scores in
 // LDS), 1 the split path (window scores by many workgroups per row into the workspace, then one
-// workgroup per row selects), -1 neither (multi-row or too many windows).
+// workgroup per row selects), -1 neither (many rows per group or too many windows).
 int select_decode_path(int64_t rows, int32_t n_q, int64_t q_pos0, int32_t n_init, int32_t n_local, WinGrid grid);
 // The split decode path's scoring launch alone (its selection runs in decode_topk_row).
 hipError_t launch_decode_split_scores(const SelectArgs& a, hipStream_t stream);
