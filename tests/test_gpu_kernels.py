@@ -76,6 +76,49 @@ def test_attention_tiles(dev, G, n_q, T, k, scale, hot):
     say(f"  max err {worst:.3g} ({compare_attention.last_tight_ratio:.3f} of the tight bar)")
 
 
+# Caches that end inside a block hold anything past the last token: NaN there must not reach the output.  The
+# tile kernel (16 and more rows), the per-row kernels (up to 5 heads, and 6 and more), and the fused decode
+# step over the same sets; last tokens in both halves of a block and at their edges, in the chunk's
+# first row's block and after it.
+@pytest.mark.parametrize("G,n_q,T", [
+    (4, 16, 4097), (4, 40, 3000), (16, 16, 2081), (16, 130, 2110), (8, 33, 4096 - 33), (2, 70, 1000), (1, 200, 900), (16, 20, 10),
+    (4, 3, 2000), (6, 1, 2049), (7, 1, 4096 - 33), (16, 1, 2080), (16, 1, 2081), (8, 1, 4095), (7, 5, 3003), (4, 1, 4063), (16, 1, 1)])
+def test_attention_unwritten_tail(dev, G, n_q, T):
+    say(f"attention unwritten tail G{G} n_q{n_q} T{T}")
+    n_q = min(n_q, T)
+    B, H, k, q_pos0, t_cap = 2, 2, 12, T - n_q, -(-T // 64) * 64
+    s, o = shapes(B, H, G, k, t_cap, t_cap // 64)
+    kc, v = (inputs.normal_bf16((B, H, t_cap, 128), 11, i) for i in range(2))
+    q = inputs.normal_bf16((B, H * G, n_q, 128), 11, 2)
+    f = inputs.normal_bf16((B, H, n_q, 128), 11, 3)
+    k16, v16 = inputs.to_u16(kc).copy(), inputs.to_u16(v).copy()  # finite, for the oracle
+    kc[:, :, T:] = math.nan
+    v[:, :, T:] = math.nan
+    cmp16 = oracle.compress_keys(o, k16, t_cap, 0, t_cap // 64)  # (64, 64) windows: those of the blocks before the last
+    kd, vd, qd, fd, cd = kc.to(dev), v.to(dev), q.to(dev), f.to(dev), inputs.from_u16(cmp16, dev)
+    sel = torch.full((B, H, n_q, k), 777, dtype=torch.int16, device=dev)
+    cnt = torch.full((B, H, n_q), 777, dtype=torch.int16, device=dev)
+    out = torch.full((B, H * G, n_q, 128), math.nan, dtype=torch.bfloat16, device=dev)
+    ws = [torch.empty(max(sp.sparda_workspace_size(s, op, n_q, q_pos0), 16), dtype=torch.uint8, device=dev)
+          for op in (sp.SPARDA_OP_FORECAST_SELECT, sp.SPARDA_OP_SPARSE_ATTN)]
+    sp.sparda_forecast_select(s, fd, n_q, q_pos0, cd, sel, cnt, ws[0])
+    sp.sparda_sparse_attn(s, qd, n_q, q_pos0, kd, vd, 0, sel, cnt, SCALE, out, ws[1])
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy()
+    assert np.isfinite(got).all(), f"{int((~np.isfinite(got)).sum())} of {got.size} outputs are not finite"
+    sets, counts = sel.cpu().numpy(), cnt.cpu().numpy()
+    q16 = inputs.to_u16(q)
+    ref = oracle.sparse_attn(o, q16, n_q, q_pos0, k16, v16, 0, sets, counts, SCALE)
+    wab = oracle.sparse_attn(o, q16, n_q, q_pos0, k16, abs_bits(v16), 0, sets, counts, SCALE)
+    compare_attention(got, ref, "tail", wab)
+    if n_q == 1:
+        sel2, cnt2, out2 = torch.empty_like(sel), torch.empty_like(cnt), torch.full_like(out, math.nan)
+        w = torch.empty(max(sp.sparda_workspace_size(s, sp.SPARDA_OP_DECODE_STEP, 1, q_pos0), 16), dtype=torch.uint8, device=dev)
+        sp.sparda_decode_step(s, fd, q_pos0, cd, qd, kd, vd, SCALE, sel2, cnt2, out2, w)
+        torch.cuda.synchronize()
+        assert torch.equal(sel2, sel) and torch.equal(cnt2, cnt) and torch.equal(out2.view(torch.int16), out.view(torch.int16))
+
+
 # The indexer-training target over chunks of keys: 1, 2 to 3 and 5 or more units of 64 / G rows (the
 # wavefronts of a workgroup share a unit's keys below 4), one and several chunks, and keys late in the
 # context whose logits lie up to 2^100 above the first tile's (the sums are formed again from the
