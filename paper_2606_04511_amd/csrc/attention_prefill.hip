@@ -175,9 +175,9 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(AttnArgs a,
   // normalisation by l, accumulated against the same reference, makes the result exact.
   constexpr float kHeadroom = 64.f;
   const int blk0 = (int)(p0 / kBlock);  // blocks >= blk0 may hold tokens after some row's position
-  // The chunk's last position: the caches hold no token after it, and whatever lies there (NaN, say) must
-  // not meet the P = 0 of those tokens in the matrix cores.
-  const int last_blk = (int)((a.q_pos0 + a.n_q - 1) / kBlock), last_tok = (int)((a.q_pos0 + a.n_q - 1) % kBlock);
+  // The chunk's last position.  Whatever the caches hold after it (NaN, say) must not meet the P = 0 of
+  // those tokens in the matrix cores.
+  const int chunk_last = (int)(a.q_pos0 + a.n_q - 1);
 
   // Operand addresses: K row 16 mt + c, piece (4 ks + q) ^ c; V rows 16 mt + 4 q + r (lane's r = c
   // / 4), dims 16 md + 4 (c % 4) .. + 3, piece (2 md + (c / 2) % 2) ^ 2 (row % 8).  Both swizzles
@@ -202,8 +202,19 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(AttnArgs a,
     const uint32_t d = ring_at + slot * kPaSlot;
 #pragma unroll
     for (int u = 0; u < 4; ++u) lds_load16(kp + off + u * 4096, k_off, d + u * 4096);
+    const int last_tok = chunk_last - j * kBlock;
+    if (last_tok >= kBlock - 1) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) lds_load16(vp + off + u * 4096, v_off, d + kBlock * kHeadDim * 2 + u * 4096);
+      for (int u = 0; u < 4; ++u) lds_load16(vp + off + u * 4096, v_off, d + kBlock * kHeadDim * 2 + u * 4096);
+    } else {  // tokens past the chunk's end: its last token's V in their place
+      int t = lane >> 4;
+      __asm__ __volatile__("" : "+v"(t));  // the offsets here: held across the loop they would spill
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int back = max(16 * u + 4 * wave + t - last_tok, 0);
+        lds_load16(vp + off, v_off + (uint32_t)((16 * u - back) * kHeadDim * 2), d + kBlock * kHeadDim * 2 + u * 4096);
+      }
+    }
   };
 
   __syncthreads();  // union list and bitmaps complete
@@ -249,13 +260,6 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(AttnArgs a,
         // this wavefront's rows of block it have landed and its reads of block it - 1 have returned;
         // then block it + 1 is requested into the other slot, which every wavefront has left
         lds_loads_landed();
-        if (j == last_blk && last_tok < kBlock - 1) {  // V rows past the chunk's end: zeros (of those it brought itself)
-          char* v_own = reinterpret_cast<char*>(ring) + (it & 1) * kPaSlot + kBlock * kHeadDim * 2 + wave * 1024 + lane * 16;
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (16 * u + s_tok > last_tok) *reinterpret_cast<uint4*>(v_own + u * 4096) = make_uint4(0u, 0u, 0u, 0u);
-          lds_loads_landed();
-        }
         __builtin_amdgcn_s_barrier();
         __asm__ __volatile__("" ::: "memory");
         if (it + 1 < nu) {
