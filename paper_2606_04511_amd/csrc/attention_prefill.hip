@@ -19,19 +19,19 @@
 //        S^T = K Q^T on v_mfma_f32_16x16x32_bf16 (M = 16 tokens, N = 16 query-heads, K = 32
 //        dims); query-heads whose row does not list j, and tokens after the row's position, are
 //        masked; online softmax in the exp2 domain;
-//        O^T += V^T P^T on the same MFMA (M = 16 head dims, N = 16 query-heads, K = 32 tokens), and
-//        the sums of P by two more of them against a tile of ones.
+//        O^T += V^T P^T on the same MFMA (M = 16 head dims, N = 16 query-heads, K = 32 tokens); the
+//        denominators sum P in float32, before it is rounded for the product.
 //      P needs no data movement between the two products: k slot 4 x + i of lane group q is token
 //      16 (2 s + x) + 4 q + i, the order in which an S^T accumulator lane holds its scores.
 //
-// What bounds it: issue.  Per visited N-tile a wavefront issues 34 MFMAs (544 cycles) and about 98
+// What bounds it: issue.  Per visited N-tile a wavefront issues 32 MFMAs (512 cycles) and about 115
 // VALU instructions, which overlap only in part (a probe: two VALU instructions hide under one
 // 16-cycle MFMA, the third costs 8 cycles), and a block ends with its busiest wavefront (1.28 to
 // 1.5 times the mean).  Reading every block from a 256 KiB footprint instead changes 4 %, so memory is
 // not the limit.  A 32K prefill of 32 / 8 heads, k = 64, neighbouring rows sharing 0.8 of their
-// Forecast variance: 3.83 ms, 535 TFLOP/s of attended pairs (5.89 ms with K and V staged through
-// registers, V transposed on the way, and a branch around every product); the last 8192 rows of 32
-// / 2 heads, k = 96: 1.25 ms (1.97).  Tried and slower: eight wavefronts with a ring of four blocks
+// Forecast variance: 3.95 ms, 519 TFLOP/s of attended pairs (5.93 ms with K and V staged through
+// registers, V transposed on the way, and a branch around every product; 3.88 with the denominators
+// summed by two MFMAs of the rounded P against ones, which holds fewer bits of them).  Tried and slower: eight wavefronts with a ring of four blocks
 // and one barrier per block (4.70 ms); one wavefront bringing the blocks for 7, 11 or 15 others without
 // barriers (4.0 ms; the ring is too short to even out the wavefronts; 1.12 ms at 16 heads per group);
 // one N-tile per wavefront on 16 wavefronts (4.33 ms).
@@ -158,12 +158,12 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(AttnArgs a,
   // a scale of zero (uniform weights): the smallest positive scale instead, so that masked scores
   // (-inf) keep weight 0
   if (zscale == 0.f) zscale = __FLT_MIN__;
-  float m_run[kNt];
-  f32x4 accl[kNt], acc[kNt][8];
+  float m_run[kNt], l_run[kNt];
+  f32x4 acc[kNt][8];
 #pragma unroll
   for (int nt = 0; nt < kNt; ++nt) {
     m_run[nt] = -INFINITY;
-    accl[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    l_run[nt] = 0.f;
 #pragma unroll
     for (int md = 0; md < 8; ++md) acc[nt][md] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
@@ -321,9 +321,6 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(AttnArgs a,
           for (int x = 0; x < 4; ++x) vf[md][x] = lds_read_tr16(vb + 16 * x * kHeadDim * 2 + (va0 ^ ((4 * h + md) << 5)));
       };
       read_v(0);
-      uint32_t one2 = 0x3f803f80u;  // two bf16 ones
-      __asm__ __volatile__("" : "+v"(one2));
-      const bf16x8 ones = as_bf16x8(make_uint4(one2, one2, one2, one2));
       bf16x8 pb[kNt][2];
 #pragma unroll
       for (int nt = 0; nt < kNt; ++nt) {
@@ -335,6 +332,12 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(AttnArgs a,
         for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
           for (int i = 0; i < 4; ++i) pz[mt][i] = __builtin_amdgcn_exp2f(fmaf(st[nt][mt][i], zscale, off));
+        float psum = 0.f;  // of the lane's tokens, before P is rounded
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) psum += pz[mt][i];
+        l_run[nt] += psum;
         // B operand of k-step s2: slot 4 x + i holds token 16 (2 s2 + x) + 4 q + i
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
@@ -344,7 +347,6 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(AttnArgs a,
           w.z = pack_bf16(pz[2 * s2 + 1][0], pz[2 * s2 + 1][1]);
           w.w = pack_bf16(pz[2 * s2 + 1][2], pz[2 * s2 + 1][3]);
           pb[nt][s2] = as_bf16x8(w);
-          accl[nt] = mfma16x16x32(ones, pb[nt][s2], accl[nt]);  // the column's sum of P in every row
         }
       }
       __builtin_amdgcn_s_setprio(0);
@@ -375,7 +377,7 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(AttnArgs a,
       if (!(m > m_run[nt] + kHeadroom)) continue;
       const float alpha = __builtin_amdgcn_exp2f(m_run[nt] - m);
       m_run[nt] = m;
-      accl[nt] *= alpha;
+      l_run[nt] *= alpha;
 #pragma unroll
       for (int md = 0; md < 8; ++md) acc[nt][md] *= alpha;
     }
@@ -384,8 +386,10 @@ __global__ __launch_bounds__(kPaThreads, 2) void prefill_attn_kernel(AttnArgs a,
   // ---- normalise and store: lane (c, q) holds dims 16 md + 4 q + i of its column
 #pragma unroll
   for (int nt = 0; nt < kNt; ++nt) {
+    float l = l_run[nt];
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
     if (rl + nt * RN >= nrows) continue;
-    const float l = accl[nt][0];
     const float inv = l > 0.f ? 1.f / l : 0.f;
     uint16_t* orow = a.o + ((bm * G + c % G) * a.n_q + r0 + rl + nt * RN) * kHeadDim + 4 * q;
 #pragma unroll

@@ -76,6 +76,33 @@ def test_attention_tiles(dev, G, n_q, T, k, scale, hot):
     say(f"  max err {worst:.3g} ({compare_attention.last_tight_ratio:.3f} of the tight bar)")
 
 
+# The tile kernel's denominators sum P before it is rounded to bf16.  A row's first four tokens have weight 1 and V = 1,
+# its others weight P and V = 0, so the output is 4 / (4 + n P), with P just above the middle of two bf16
+# values: rounded, it would move the output by up to 2^-8.  The output is the nearest bf16 of a value within 2^-14 of the
+# exact one (float32's exponential, sums and the logit log2 P of at most 3: a few 2^-22).
+@pytest.mark.parametrize("G", [1, 2, 4, 8, 16])
+@pytest.mark.parametrize("exponent", [1, 2, 3])
+def test_attention_tile_denominator(dev, G, exponent):
+    say(f"attention denominators G{G} P 2^-{exponent}")
+    n_q, H, q_pos0 = 40, 2, 20
+    P = (1 + 2.0 ** -8 * 1.05) * 2.0 ** -exponent
+    s, _ = shapes(1, H, G, 1, 64, 1, n_init=0, n_local=1)
+    q = torch.zeros(1, H * G, n_q, 128, dtype=torch.bfloat16, device=dev)
+    q[..., 0] = 1.0
+    k, v = torch.zeros(1, H, 64, 128, dtype=torch.bfloat16, device=dev), torch.zeros(1, H, 64, 128, dtype=torch.bfloat16, device=dev)
+    k[:, :, 4:, 0] = -1.0
+    v[:, :, :4] = 1.0
+    sel = torch.zeros(1, H, n_q, 1, dtype=torch.int16, device=dev)
+    out = torch.full((1, H * G, n_q, 128), math.nan, dtype=torch.bfloat16, device=dev)
+    sp.sparda_sparse_attn(s, q, n_q, q_pos0, k, v, 0, sel, torch.ones(1, H, n_q, dtype=torch.int16, device=dev), -math.log(P),
+                          out, torch.empty(16, dtype=torch.uint8, device=dev))
+    torch.cuda.synchronize()
+    ref = 4 / (4 + (q_pos0 + torch.arange(n_q, dtype=torch.float64) + 1 - 4) * P)[None, None, :, None]
+    got = out.double().cpu()
+    for side, ok in ((1 - 2.0 ** -14, torch.ge), (1 + 2.0 ** -14, torch.le)):
+        assert bool(ok(got, (ref * side).to(torch.bfloat16).double()).all()), float(((got - ref).abs() / ref).max())
+
+
 # Caches that end inside a block hold anything past the last token: NaN there must not reach the output.  The
 # tile kernel (16 and more rows), the per-row kernels (up to 5 heads, and 6 and more), and the fused decode
 # step over the same sets; last tokens in both halves of a block and at their edges, in the chunk's
