@@ -103,6 +103,34 @@ def test_attention_tile_denominator(dev, G, exponent):
         assert bool(ok(got, (ref * side).to(torch.bfloat16).double()).all()), float(((got - ref).abs() / ref).max())
 
 
+# The reference of a row's weights follows its scores closely, so that large values stay in float32's range: one block's
+# scores lie `rise` log2 units above those before it, its V at 2^105.  Uniform weights inside the block, so the
+# output is V's value; an accumulator against the earlier blocks' reference would reach 2^(105 + rise).
+@pytest.mark.parametrize("G,n_q", [(4, 20), (16, 17), (8, 1), (4, 1)])
+@pytest.mark.parametrize("rise", [7.0, 12.0, 40.0, 63.0])
+def test_attention_large_values(dev, G, n_q, rise):
+    say(f"attention large values G{G} n_q{n_q} rise {rise}")
+    H, T, k = 2, 64 * 4, 4
+    s, _ = shapes(1, H, G, k, T, 4, n_init=0, n_local=1)
+    q = torch.zeros(1, H * G, n_q, 128, dtype=torch.bfloat16, device=dev)
+    q[..., 0] = 1.0
+    kc = torch.zeros(1, H, T, 128, dtype=torch.bfloat16, device=dev)
+    v = torch.zeros(1, H, T, 128, dtype=torch.bfloat16, device=dev)
+    kc[:, :, 128:192, 0] = 1.0
+    v[:, :, 128:192] = 2.0 ** 105
+    sel = torch.arange(k, dtype=torch.int16, device=dev).expand(1, H, n_q, k).contiguous()
+    cnt = torch.full((1, H, n_q), k, dtype=torch.int16, device=dev)
+    ws = torch.empty(max(sp.sparda_workspace_size(s, sp.SPARDA_OP_SPARSE_ATTN, n_q, T - n_q), 16), dtype=torch.uint8, device=dev)
+    out = torch.full((1, H * G, n_q, 128), math.nan, dtype=torch.bfloat16, device=dev)
+    sp.sparda_sparse_attn(s, q, n_q, T - n_q, kc, v, 0, sel, cnt, rise * math.log(2), out, ws)
+    torch.cuda.synchronize()
+    # every position is in block 3: three blocks of weight 1 (the last cut at the row), one of 2^rise
+    others = 128 + 64 - n_q + 1 + torch.arange(n_q, dtype=torch.float64)
+    ref = 2.0 ** 105 * 64 / (64 + others * 2.0 ** -rise)
+    err = ((out.double().cpu() - ref[None, None, :, None]).abs() / ref[None, None, :, None]).max()
+    assert float(err) <= 2.0 ** -8, float(err)
+
+
 # Caches that end inside a block hold anything past the last token: NaN there must not reach the output.  The
 # tile kernel (16 and more rows), the per-row kernels (up to 5 heads, and 6 and more), and the fused decode
 # step over the same sets; last tokens in both halves of a block and at their edges, in the chunk's
