@@ -460,16 +460,17 @@ __device__ __forceinline__ void attend_row_wide(const AttnArgs& a, int64_t row, 
       }
     bmax = fmaxf(bmax, __shfl_xor(bmax, 16, 64));
     bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-    const float m_new = fmaxf(m_run, bmax);  // the half's first token is always <= p: finite
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    const float m_new = fmaxf(m_run, bmax);
+    const float ref = m_new > -INFINITY ? m_new : 0.f;  // every score so far -inf: weights 0
+    const float alpha = __builtin_amdgcn_exp2f(m_run - ref);
     uint32_t pw[2][2];  // bf16 pairs of tile tt: (i = 0, 1), (i = 2, 3)
     float psum = 0.f;
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
       for (int q2 = 0; q2 < 2; ++q2) {
-        const uint32_t w = pack_bf16(__builtin_amdgcn_exp2f(z[tt][2 * q2] - m_new),
-                                     __builtin_amdgcn_exp2f(z[tt][2 * q2 + 1] - m_new));
+        const uint32_t w = pack_bf16(__builtin_amdgcn_exp2f(z[tt][2 * q2] - ref),
+                                     __builtin_amdgcn_exp2f(z[tt][2 * q2 + 1] - ref));
         psum += bf16lo(w) + bf16hi(w);
         pw[tt][q2] = w;
       }

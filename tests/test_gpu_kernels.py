@@ -131,6 +131,34 @@ def test_attention_large_values(dev, G, n_q, rise):
     assert float(err) <= 2.0 ** -8, float(err)
 
 
+# Tokens whose scores overflow to -inf have weight 0, also where they fill a half of a block (the wide kernel walks halves), the
+# first one of a row, or all of a row's first block but one token.
+@pytest.mark.parametrize("G,n_q", [(6, 1), (16, 1), (7, 3), (4, 1), (4, 16), (16, 20)])
+@pytest.mark.parametrize("hidden", [(0, 32), (32, 64), (1, 64)])
+def test_attention_infinite_scores(dev, G, n_q, hidden):
+    say(f"attention infinite scores G{G} n_q{n_q} hidden {hidden}")
+    H, T, k = 2, 64 * 3, 3
+    s, _ = shapes(1, H, G, k, T, 3, n_init=0, n_local=1)
+    q = torch.zeros(1, H * G, n_q, 128, dtype=torch.bfloat16, device=dev)
+    q[..., 0] = 2.0 ** 100
+    kc = torch.zeros(1, H, T, 128, dtype=torch.bfloat16, device=dev)
+    v = inputs.normal_bf16((1, H, T, 128), 12, 0).to(dev)
+    for j in range(2):  # every block but the row's own
+        kc[:, :, 64 * j + hidden[0]:64 * j + hidden[1], 0] = -2.0 ** 100
+    sel = torch.arange(k, dtype=torch.int16, device=dev).expand(1, H, n_q, k).contiguous()
+    cnt = torch.full((1, H, n_q), k, dtype=torch.int16, device=dev)
+    ws = torch.empty(max(sp.sparda_workspace_size(s, sp.SPARDA_OP_SPARSE_ATTN, n_q, T - n_q), 16), dtype=torch.uint8, device=dev)
+    out = torch.full((1, H * G, n_q, 128), math.nan, dtype=torch.bfloat16, device=dev)
+    sp.sparda_sparse_attn(s, q, n_q, T - n_q, kc, v, 0, sel, cnt, SCALE, out, ws)
+    torch.cuda.synchronize()
+    t = torch.arange(T)
+    for r in range(n_q):  # uniform weights over the visible tokens
+        seen = (t <= T - n_q + r) & ((t >= 128) | (t % 64 < hidden[0]) | (t % 64 >= hidden[1]))
+        ref = v[0].double().cpu()[:, seen].mean(1).repeat_interleave(G, 0)
+        err = (out[0, :, r].double().cpu() - ref).abs().max()
+        assert float(err) <= 2.0 ** -8 * float(ref.abs().max()) + 1e-5, f"row {r}: {float(err)}"
+
+
 # Caches that end inside a block hold anything past the last token: NaN there must not reach the output.  The
 # tile kernel (16 and more rows), the per-row kernels (up to 5 heads, and 6 and more), and the fused decode
 # step over the same sets; last tokens in both halves of a block and at their edges, in the chunk's
