@@ -87,8 +87,9 @@ static hipError_t launch_rowwise_scores(const SelectArgs& a, int64_t rows, int n
 // rows run the radix passes over the workspace (rowwise_topk_kernel).
 constexpr int kRowTopkMax = 4096;
 
-// kPooled: the row's block scores are in the workspace, candidate 0 at slot 0 (block_score_kernel);
-// otherwise its window scores, window wf at slot 0.
+// kPooled: the row's block scores are in the workspace, candidate 0 at slot 0 (block_score_kernel, or any
+// scores on the one-key-per-block grid); otherwise its window scores on the (32, 16) grid, window wf at
+// slot 0.
 template <bool kPooled>
 __device__ __forceinline__ float candidate_score(const SelectArgs& a, const float* sc, int cand_lo, int i, int32_t wf,
                                                  int32_t wvis) {
@@ -118,9 +119,13 @@ __global__ __launch_bounds__(256) void rowwise_topk_kernel(SelectArgs a, int64_t
 // The same for rows of at most 64 R candidates, their keys in registers (reg_topk_emit: candidate
 // 64 i + lane is key i of the lane).
 //
-// What bounds it: VALU issue, about 1000 instructions per row of 2048.  32 768 rows of 2045 block
-// scores: 120-140 us; pooling window scores into LDS and four radix passes there took 730 us.
-template <int R, bool kPooled>
+// What bounds it: for many rows VALU issue (about 1000 instructions per row of 2048, half the time) and the
+// row's one load latency, for few rows latency alone; so a row holds no more slots than it has candidates
+// and its loads are batched.  32 768 rows of 2045 block scores 120-125 us (pooling window scores into LDS
+// and four radix passes there 730); window scores of 8000 rows of 30, 122, 247 and 1560 candidates 7.3,
+// 12.3, 16.3 and 74 us (26, 34, 35 and 96 with at least 16 slots and all loads at once; 10.8, 18.6, 34 and
+// 140 by radix passes), of 128 rows of 30 candidates 3.8 (9.4; 5.5).
+template <int R, bool kPooled, bool kScores>
 __global__ __launch_bounds__(256) void row_topk_kernel(SelectArgs a, int64_t n_rows) {
   __shared__ uint32_t list[4][64];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -139,48 +144,84 @@ __global__ __launch_bounds__(256) void row_topk_kernel(SelectArgs a, int64_t n_r
   }
   if (n <= 0) return;
   const float* sc = a.ws + row * a.ws_stride;
-  int32_t wf, wl;
-  row_windows(g, a.grid, p, &wf, &wl);
-  const int32_t wvis = grid_win_vis(a.grid, p);
-  uint32_t key[R];  // slots past the row's candidates: key 0, below every score
-  // A block's windows on a grid that divides the block are 64 / s - 1 + l / s.  Up to five of them
-  // ((32, 16) has five) are loaded without a loop, repeats past the last one: every slot's loads are
-  // then requested before the first is waited for.
-  if (!kPooled && kBlock % a.grid.s == 0 && a.grid.l % a.grid.s == 0 && kBlock / a.grid.s + a.grid.l / a.grid.s <= 6) {
+  // Slots past the row's candidates: key 0, below every score.  The loads are requested kBatch slots at a time
+  // before the first is waited for, repeats of the last candidate past the end; the empty asm keeps the
+  // compiler from moving each into a branch of its own.
+  uint32_t key[R];
+  if constexpr (kPooled) {
+    constexpr int kBatch = R < 16 ? R : 16;
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const int c = 64 * i + lane, j = g.cand_lo + min(c, C - 1);
-      const int lo = grid_win_lo(a.grid, j), hi = max(lo, min(grid_win_hi(a.grid, j), wvis));
-      float x = sc[lo - wf];
+    for (int i0 = 0; i0 < R; i0 += kBatch) {
+      float x[kBatch];
 #pragma unroll
-      for (int u = 1; u < 5; ++u) x = fmaxf(x, sc[min(lo + u, hi) - wf]);
-      key[i] = c < C ? score_key(x) : 0u;
+      for (int i = 0; i < kBatch; ++i) x[i] = sc[min(64 * (i0 + i) + lane, C - 1)];
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        __asm__ __volatile__("" : "+v"(x[i]));
+        key[i0 + i] = 64 * (i0 + i) + lane < C ? score_key(x[i]) : 0u;
+      }
     }
-  } else {
+  } else {  // block j's windows are 4 j - 1 .. 4 j + 3: five loads, repeats past the first and the last one
+    constexpr int kBatch = R < 8 ? R : 8;
+    constexpr WinGrid kGrid{32, 16};
+    const int32_t wf = grid_win_lo(kGrid, g.cand_lo), wvis = grid_win_vis(kGrid, p);
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const int c = 64 * i + lane;
-      const float x = candidate_score<kPooled>(a, sc, g.cand_lo, min(c, C - 1), wf, wvis);
-      key[i] = c < C ? score_key(x) : 0u;
+    for (int i0 = 0; i0 < R; i0 += kBatch) {
+      float x[kBatch][5];
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int lo = 4 * (g.cand_lo + min(64 * (i0 + i) + lane, C - 1)) - 1;
+#pragma unroll
+        for (int u = 0; u < 5; ++u) x[i][u] = sc[max(min(lo + u, wvis), 0) - wf];
+      }
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+#pragma unroll
+        for (int u = 0; u < 5; ++u) __asm__ __volatile__("" : "+v"(x[i][u]));
+        const float m = fmaxf(fmaxf(fmaxf(x[i][0], x[i][1]), fmaxf(x[i][2], x[i][3])), x[i][4]);
+        key[i0 + i] = 64 * (i0 + i) + lane < C ? score_key(m) : 0u;
+      }
     }
   }
-  reg_topk_emit<R, kPooled>(key, C, n, g.cand_lo, out, list[wave]);
+  if constexpr (R == 1)
+    lane_topk_emit(key[0], C, n, g.cand_lo, out);
+  else
+    reg_topk_emit<R, kScores>(key, C, n, g.cand_lo, out, list[wave]);
 }
 
-template <bool kPooled>
+template <bool kPooled, bool kScores>
 static hipError_t launch_topk(const SelectArgs& a, hipStream_t stream) {
   const int64_t rows = (int64_t)a.batch * a.n_kv_heads * a.n_q;
   const int C = row_geom(a.q_pos0 + a.n_q - 1, a.n_init, a.n_local, a.k_total).n_cand;  // the last row has the most
   const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
+  if constexpr (!kScores) {  // Forecast scores come here from 513 candidates on only
+    if (C <= 512) {
+      if (C <= 64)
+        hipLaunchKernelGGL((row_topk_kernel<1, kPooled, false>), grid, block, 0, stream, a, rows);
+      else if (C <= 128)
+        hipLaunchKernelGGL((row_topk_kernel<2, kPooled, false>), grid, block, 0, stream, a, rows);
+      else if (C <= 256)
+        hipLaunchKernelGGL((row_topk_kernel<4, kPooled, false>), grid, block, 0, stream, a, rows);
+      else
+        hipLaunchKernelGGL((row_topk_kernel<8, kPooled, false>), grid, block, 0, stream, a, rows);
+      return hipGetLastError();
+    }
+  }
   if (C <= 1024)
-    hipLaunchKernelGGL((row_topk_kernel<16, kPooled>), grid, block, 0, stream, a, rows);
+    hipLaunchKernelGGL((row_topk_kernel<16, kPooled, kScores>), grid, block, 0, stream, a, rows);
   else if (C <= 2048)
-    hipLaunchKernelGGL((row_topk_kernel<32, kPooled>), grid, block, 0, stream, a, rows);
+    hipLaunchKernelGGL((row_topk_kernel<32, kPooled, kScores>), grid, block, 0, stream, a, rows);
   else if (C <= kRowTopkMax)
-    hipLaunchKernelGGL((row_topk_kernel<64, kPooled>), grid, block, 0, stream, a, rows);
+    hipLaunchKernelGGL((row_topk_kernel<64, kPooled, kScores>), grid, block, 0, stream, a, rows);
   else
     hipLaunchKernelGGL(rowwise_topk_kernel<kPooled>, grid, block, 0, stream, a, rows);
   return hipGetLastError();
+}
+
+// Window scores in the workspace: on the one-key-per-block grid they are the blocks'.
+template <bool kScores>
+static hipError_t launch_window_topk(const SelectArgs& a, hipStream_t stream) {
+  return grid_is_blocks(a.grid) ? launch_topk<true, kScores>(a, stream) : launch_topk<false, kScores>(a, stream);
 }
 
 // ---- fused decode path ---------------------------------------------------------------------
@@ -279,7 +320,7 @@ bool select_needs_scratch(int64_t rows, int32_t n_q, int64_t q_pos0, int32_t n_i
   return path == kPathRowwise || path == kPathDecodeSplit;
 }
 
-hipError_t launch_rowwise_topk(const SelectArgs& a, hipStream_t stream) { return launch_topk<false>(a, stream); }
+hipError_t launch_rowwise_topk(const SelectArgs& a, hipStream_t stream) { return launch_window_topk<false>(a, stream); }
 
 hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
   const int64_t rows = (int64_t)a.batch * a.n_kv_heads * a.n_q;
@@ -301,13 +342,13 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
   if (gl.n_cand > 0 && wl >= wf && a.n_q >= kTileScoreMinRows && tile_grid(a.grid)) {
     // many rows: 64-row units score on MFMA, each key fragment shared by the unit's rows
     hipError_t e = launch_block_scores(a, stream);
-    return e != hipSuccess ? e : launch_topk<true>(a, stream);
+    return e != hipSuccess ? e : launch_topk<true, true>(a, stream);
   } else if (gl.n_cand > 0 && wl >= wf) {  // the last row scores the most windows
     const int n_chunks = (wl - wf + 1 + 255) / 256;
     hipError_t e = launch_rowwise_scores(a, rows, n_chunks, stream);
     if (e != hipSuccess) return e;
   }
-  if (path != kPathDecodeSplit) return launch_topk<false>(a, stream);
+  if (path != kPathDecodeSplit) return launch_window_topk<true>(a, stream);
   hipLaunchKernelGGL(decode_topk_kernel, dim3((unsigned)rows), dim3(kDecThreads), 0, stream, a);
   return hipGetLastError();
 }

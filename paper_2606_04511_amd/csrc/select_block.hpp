@@ -208,6 +208,24 @@ __device__ __forceinline__ void radix_topk_emit(const float* bs, int C, int n_ta
   }
 }
 
+// One wavefront's exact top-k over C <= 64 keys, candidate `lane` in the lane: cand_lo + the n best by
+// (key, lower index) in ascending order to out.
+__device__ __forceinline__ void lane_topk_emit(uint32_t mine, int C, int n, int cand_lo, int16_t* out) {
+  const int lane = threadIdx.x & 63;
+  int rank = 0;  // keys that come first: larger, or equal at a lower index (lanes past C come after all)
+  for (int j0 = 0; j0 < C; j0 += 16) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const uint32_t o = (uint32_t)readlane_i((int)mine, j0 + j);
+      rank += o > mine ? 1 : 0;
+      rank += (o == mine && j0 + j < lane) ? 1 : 0;
+    }
+  }
+  const bool chosen = lane < C && rank < n;
+  const uint64_t cb = __ballot(chosen);
+  if (chosen) out[mbcnt64(cb)] = (int16_t)(cand_lo + lane);
+}
+
 // One wavefront's exact top-k over C <= 64 R keys (order-preserving score bits) in its registers:
 // candidate 64 i + lane is key i of the lane (0, below every score, past C).  0 < n < C; writes cand_lo +
 // the chosen candidates in ascending order to out[0 .. n).  list: 64 uint32 of LDS.  The n-th
@@ -400,17 +418,7 @@ __device__ __forceinline__ void block_topk_emit(const float* bs, int C, int n_ta
   uint32_t* list = hist + 272;
   uint32_t* list_n = hist + 400;
   if (C <= kWave) {  // every score in a lane of one wavefront, ranked there; no barrier
-    if (wave == 0) {
-      const uint32_t mine = lane < C ? score_key(bs[lane]) : 0u;
-      int rank = 0;  // keys that come first: larger, or equal at a lower index
-      for (int j = 0; j < C; ++j) {
-        const uint32_t o = (uint32_t)readlane_i((int)mine, j);
-        rank += (o > mine || (o == mine && j < lane)) ? 1 : 0;
-      }
-      const bool chosen = lane < C && rank < n_take;
-      const uint64_t cb = __ballot(chosen);
-      if (chosen) chosen_out[mbcnt64(cb)] = (int16_t)(cand_lo + lane);
-    }
+    if (wave == 0) lane_topk_emit(lane < C ? score_key(bs[lane]) : 0u, C, n_take, cand_lo, chosen_out);
     return;
   }
   uint32_t kmin = 0xffffffffu, kmax = 0u;

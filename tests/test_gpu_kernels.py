@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2606_04511_amd import inputs
 from paper_2606_04511_amd import sparda as sp
-from parity import abs_bits, compare_attention, compare_selection
+from parity import abs_bits, compare_attention, compare_multihead_selection, compare_selection
 
 pytestmark = pytest.mark.gpu
 SCALE = 1.0 / math.sqrt(128)
@@ -277,6 +277,45 @@ def test_rowwise_select_edges(dev, C, n_q, k, n_init, n_local, grid, levels):
     else:
         rows = [(0, m, r) for m in range(H) for r in sorted({0, 1, n_q // 2, n_q - 2, n_q - 1})]
         say("  rows %d, tie swaps %d" % compare_selection(o, f16, kc16, n_q, q_pos0, sel, cnt, rows))
+
+
+# The multi-head selector's multi-row calls: the candidate counts at which the top-k takes more keys per lane (64, 128,
+# 256, 512, 1024, 2048) and the most it holds, both key grids (block scores read as they are, windows pooled).
+# `levels` draws the scores from so many values, so that ties decide and the sets must be the oracle's.
+@pytest.mark.parametrize("C,n_q,G,k,n_init,n_local,grid,levels", [
+    (2, 16, 4, 4, 1, 2, (64, 64), 0), (64, 17, 1, 12, 1, 2, (32, 16), 0), (65, 40, 16, 12, 0, 1, (32, 16), 0),
+    (64, 16, 4, 40, 1, 2, (64, 64), 0), (128, 130, 2, 12, 2, 2, (64, 64), 0), (129, 16, 4, 100, 1, 2, (32, 16), 0),
+    (256, 20, 8, 12, 1, 1, (32, 16), 0), (257, 16, 4, 12, 1, 2, (64, 64), 0), (512, 18, 1, 64, 0, 2, (32, 16), 0),
+    (513, 16, 4, 64, 1, 2, (32, 16), 0), (1025, 16, 1, 64, 1, 2, (32, 16), 0), (2048, 16, 4, 64, 1, 2, (64, 64), 0),
+    (2049, 17, 2, 64, 1, 1, (32, 16), 0), (4096, 16, 1, 64, 1, 2, (64, 64), 0), (63, 16, 4, 20, 1, 2, (64, 64), 2),
+    (100, 33, 1, 30, 1, 2, (32, 16), 2), (200, 16, 2, 20, 1, 2, (64, 64), 3), (500, 16, 4, 200, 1, 2, (32, 16), 5),
+    (1500, 16, 1, 64, 1, 2, (32, 16), 9)])
+def test_multihead_select_edges(dev, C, n_q, G, k, n_init, n_local, grid, levels):
+    say(f"multi-head select C{C} n_q{n_q} G{G} k{k} init {n_init} local {n_local} grid {grid} levels {levels}")
+    H, T = 2, 64 * (n_init + C + n_local) - 7  # the last row has C candidates
+    q_pos0, t_cap = T - n_q, -(-T // 64) * 64
+    nw = (T - grid[0]) // grid[1] + 1
+    s, o = shapes(1, H, G, k, t_cap, nw, n_init, n_local, grid)
+    q = inputs.normal_bf16((1, H * G, n_q, 128), 13, 0)
+    kc = inputs.normal_bf16((1, H, nw, 128), 13, 1)
+    if levels:
+        q.zero_()
+        q[..., 0] = 2.0
+        kc[..., 0] = torch.from_numpy(np.random.default_rng(C).integers(0, levels, size=(1, H, nw)).astype(np.float32)).to(kc.dtype)
+    sel = torch.full((1, H, n_q, k), 777, dtype=torch.int16, device=dev)
+    cnt = torch.full((1, H, n_q), 777, dtype=torch.int16, device=dev)
+    ws = torch.empty(max(sp.sparda_workspace_size(s, sp.SPARDA_OP_MULTIHEAD_SELECT, n_q, q_pos0), 16), dtype=torch.uint8,
+                     device=dev)
+    sp.sparda_multihead_select(s, q.to(dev), n_q, q_pos0, kc.to(dev), SCALE, sel, cnt, ws)
+    torch.cuda.synchronize()
+    sel, cnt = sel.cpu().numpy(), cnt.cpu().numpy()
+    q16, kc16 = inputs.to_u16(q), inputs.to_u16(kc)
+    if levels:
+        ref, rcnt = oracle.multihead_select(o, q16, n_q, q_pos0, kc16, SCALE)
+        assert np.array_equal(cnt, rcnt) and np.array_equal(sel, ref)
+    else:
+        rows = [(0, m, r) for m in range(H) for r in sorted({0, 1, n_q // 2, n_q - 1})]
+        say("  rows %d, tie swaps %d" % compare_multihead_selection(o, q16, kc16, n_q, q_pos0, SCALE, sel, cnt, rows))
 
 
 # Multi-row calls of few rows select one workgroup per row: the last row count and window count of that
