@@ -318,6 +318,38 @@ def test_multihead_select_edges(dev, C, n_q, G, k, n_init, n_local, grid, levels
         say("  rows %d, tie swaps %d" % compare_multihead_selection(o, q16, kc16, n_q, q_pos0, SCALE, sel, cnt, rows))
 
 
+# The multi-head selector's weights: the key counts at which the one-launch kernel takes more tiles per wavefront (256, 512
+# keys) and the most it takes (1024), ragged units of every size, the most units it takes and one more group of
+# rows (the two launches over few keys), rows that take every candidate beside rows that do not, and keys late in the
+# context whose scores lie more than 2^60 above the first ones' (the two launches form their sums again; hot
+# weights are a few 2^-10 off relatively, see the indexer-training test, and top candidates lie further apart).
+@pytest.mark.parametrize("n_keys,n_q,H,G,k,n_init,n_local,grid,hot", [
+    (33, 16, 1, 1, 4, 0, 1, (32, 16), 1.0), (255, 65, 2, 1, 12, 1, 2, (32, 16), 1.0), (256, 33, 1, 2, 12, 1, 2, (64, 64), 16.0),
+    (257, 17, 3, 4, 12, 1, 1, (32, 16), 16.0), (511, 18, 2, 8, 12, 0, 2, (64, 64), 1.0), (512, 19, 2, 16, 20, 1, 2, (32, 16), 1.0),
+    (513, 16, 1, 4, 12, 1, 2, (32, 16), 1.0), (1023, 130, 2, 2, 12, 1, 2, (32, 16), 16.0), (1024, 16, 3, 1, 12, 2, 1, (32, 16), 1.0),
+    (1025, 16, 2, 4, 12, 1, 2, (32, 16), 1.0), (40, 1024, 2, 16, 20, 1, 2, (64, 64), 1.0), (40, 1028, 2, 16, 10, 1, 2, (64, 64), 1.0),
+    (700, 514, 2, 4, 12, 1, 2, (32, 16), 1.0), (4000, 16, 2, 4, 12, 1, 2, (32, 16), 16.0), (3000, 70, 1, 1, 12, 1, 2, (32, 16), 16.0)])
+def test_multihead_select_units(dev, n_keys, n_q, H, G, k, n_init, n_local, grid, hot):
+    say(f"multi-head units {n_keys} keys n_q{n_q} H{H} G{G} k{k} init {n_init} local {n_local} grid {grid} hot {hot}")
+    T = grid[1] * (n_keys - 1) + grid[0] + 5
+    n_q = min(n_q, T)
+    q_pos0, t_cap = T - n_q, -(-T // 64) * 64
+    s, o = shapes(1, H, G, k, t_cap, n_keys, n_init, n_local, grid)
+    q = inputs.normal_bf16((1, H * G, n_q, 128), 14, 0)
+    kc = inputs.normal_bf16((1, H, n_keys, 128), 14, 1)
+    kc[:, :, n_keys * 3 // 4:] *= hot
+    sel = torch.full((1, H, n_q, k), 777, dtype=torch.int16, device=dev)
+    cnt = torch.full((1, H, n_q), 777, dtype=torch.int16, device=dev)
+    ws = torch.empty(max(sp.sparda_workspace_size(s, sp.SPARDA_OP_MULTIHEAD_SELECT, n_q, q_pos0), 16), dtype=torch.uint8,
+                     device=dev)
+    sp.sparda_multihead_select(s, q.to(dev), n_q, q_pos0, kc.to(dev), SCALE, sel, cnt, ws)
+    torch.cuda.synchronize()
+    rows = [(0, m, r) for m in range(H) for r in sorted({0, 1, 15, n_q // 3, n_q // 2, n_q - 2, n_q - 1})]
+    n, swaps = compare_multihead_selection(o, inputs.to_u16(q), inputs.to_u16(kc), n_q, q_pos0, SCALE, sel.cpu().numpy(),
+                                           cnt.cpu().numpy(), rows)
+    say(f"  rows {n}, tie swaps {swaps}")
+
+
 # Multi-row calls of few rows select one workgroup per row: the last row count and window count of that
 # rule and the first past them, groups that do and do not divide 8, a chunk that begins before the first
 # candidate exists.
