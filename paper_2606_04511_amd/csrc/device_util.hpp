@@ -223,19 +223,24 @@ __device__ __forceinline__ uint4 ld16_hint(const void* p) {
 // Written as one instruction because the builtin makes the compiler wait for every such load in
 // flight before any later LDS read; the instruction has no output register, and the caller waits
 // for it (vmcnt) before the barrier that hands the rows over.  kNt: with the non-temporal hint.
+// It sets m0, which the compiler allocates to nothing but does set before instructions of its own; the
+// clobber says so, and the compiler's note that the register is reserved is expected.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <bool kNt = false>
 __device__ __forceinline__ void lds_load16(const void* base, uint32_t off, uint32_t dst) {
   if constexpr (kNt)
     __asm__ __volatile__("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
                          :
                          : "v"(off), "s"(base), "s"(dst)
-                         : "memory");
+                         : "m0", "memory");
   else
     __asm__ __volatile__("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                          :
                          : "v"(off), "s"(base), "s"(dst)
-                         : "memory");
+                         : "m0", "memory");
 }
+#pragma clang diagnostic pop
 // Waits for every such load (and every other memory access) of the wavefront.
 __device__ __forceinline__ void lds_loads_landed() {
   __asm__ __volatile__("" ::: "memory");
