@@ -42,7 +42,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 struct HeadTileArgs {
   const uint16_t* q;      // bf16 [n_groups][G][n_q][128]
   const uint16_t* keys;   // bf16 [n_groups][key_cap][128]
-  float* part;            // row r's statistics at part + r * part_stride: [chunk][head] (reference, sum)
+  float* part;            // row r's statistics at part + r * part_stride: [chunk][sharing wavefront][head] (reference, sum)
   float* out;             // row r's weights at out + r * out_stride
   int64_t key_cap, part_stride, out_stride, q_pos0;
   int32_t n_groups, n_q;
@@ -55,9 +55,6 @@ struct HeadTileArgs {
   // first one that overlaps a candidate on (out[0] is that window)
   int32_t n_init, n_local, k_total;
 };
-
-// (reference, sum) partials per column and chunk: one per wavefront that shares the unit's keys.
-__host__ __device__ inline int head_tile_parts(const HeadTileArgs& a) { return a.n_chunks * (4 / a.unit_waves); }
 
 namespace head_tiles {
 

@@ -47,18 +47,6 @@ __device__ __forceinline__ void load_frags(const uint4* row, int h, uint4 (&x)[8
     for (int i = 0; i < 4; ++i) x[4 * u + i] = row[8 * u + 4 * h + i];
 }
 
-// One M-tile of 32 keys against both N-tiles: the products only.
-__device__ __forceinline__ void mma_tile(const uint4 (&a)[8], const uint4 (&fb)[2][8], f32x16& c0, f32x16& c1) {
-#pragma unroll
-  for (int e = 0; e < 16; ++e) c0[e] = c1[e] = 0.f;
-#pragma unroll
-  for (int s = 0; s < 8; ++s) {
-    const bf16x8 av = as_bf16x8(a[s]);
-    c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, as_bf16x8(fb[0][s]), c0, 0, 0, 0);
-    c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, as_bf16x8(fb[1][s]), c1, 0, 0, 0);
-  }
-}
-
 // One M-tile of 32 candidates against both N-tiles; folds the scores into the running maxima.
 __device__ __forceinline__ void score_tile(const uint4 (&a)[8], const uint4 (&fb)[2][8], float& run0, float& run1) {
   f32x16 c0, c1;

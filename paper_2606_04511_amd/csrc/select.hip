@@ -265,18 +265,18 @@ enum SelectPath { kPathDecode, kPathDecodeSplit, kPathTile, kPathRowwise };
 // per row.
 constexpr int64_t kDecodeSplitRows = 256;
 // Multi-row calls of few rows (verifying drafted tokens, the tail of a prompt) select like decode rows,
-// one workgroup per row: at most two rows per CU, of at most the windows that a full tile row has.
-// Measured, 80 to 4096 rows (us, this path against the tile kernels or, past 512 candidates, the
-// row-wise path): (64, 64) grid at 20K 8, 14, 26, 50 for 256, 512, 1024, 2048 rows against 22-24 for
-// any number; (32, 16) grid at 20K 13, 24, 46 for 256, 512, 1024 rows against 35-39, at 32K 17, 32, 61
-// against 55-80; (64, 64) grid at 64K 12 and 22 for 256 and 512 rows against 20-36.  At 4060 windows per
-// row ((32, 16) grid at 64K) 27 and 52 against 23-39.
+// one workgroup per row: at most two rounds (a CU holds one workgroup), of at most the windows that a full
+// tile row has.  Measured, 16 to 256 rows, then 512 (us, this path against the tile kernels or, past 512
+// candidates, the row-wise path): (64, 64) grid at 2K 5.7 and 8.6 against 10-11, 4K 7.1 and 10.2 against
+// 10-13, 8K 6.9 and 12.4 against 11-17, 20K 7.3 and 13.3 against 12-23, 32K 7.7 and 14.2 against 20-22,
+// 64K 12 and 22 against 20-36; (32, 16) grid at 2K 6.5 and 10.3 against 12-16, 4K 7.8 and 11.6 against
+// 15-17, 8K 8.2 and 15.4 against 20-22, 20K 12 and 23 against 28-34, 32K 16 and 32 against 41-46.  1024
+// rows at 20K 26 against 22-24 and 46 against 35-39.  At 4060 windows per row ((32, 16) grid at 64K) 27 and
+// 52 for 256 and 512 rows against 23-39.
 constexpr int64_t kFewRows = 512;
 constexpr int64_t kFewRowsWindows = 4 * kSelTileMaxCand + 1;
 // Multi-row calls on the row-wise path with at least this many rows score on MFMA.
 constexpr int32_t kTileScoreMinRows = 16;
-
-static bool tile_grid(WinGrid grid) { return grid_is_blocks(grid) || (grid.l == 32 && grid.s == 16); }
 
 static SelectPath select_path(int64_t rows, int32_t n_q, int64_t q_pos0, int32_t n_init, int32_t n_local,
                               WinGrid grid) {
@@ -292,8 +292,8 @@ static SelectPath select_path(int64_t rows, int32_t n_q, int64_t q_pos0, int32_t
     return rows < kDecodeSplitRows && nw >= 1024 ? kPathDecodeSplit : kPathDecode;
   }
   if (rows <= kFewRows && nw <= kFewRowsWindows) return kPathDecode;  // at most 2561 floats
-  // multi-row: the fused tile kernel serves both grids up to kSelTileMaxCand candidates per row
-  return tile_grid(grid) && g.n_cand <= kSelTileMaxCand ? kPathTile : kPathRowwise;
+  // multi-row: the fused tile kernel serves up to kSelTileMaxCand candidates per row
+  return g.n_cand <= kSelTileMaxCand ? kPathTile : kPathRowwise;
 }
 
 int select_decode_path(int64_t rows, int32_t n_q, int64_t q_pos0, int32_t n_init, int32_t n_local, WinGrid grid) {
@@ -314,8 +314,7 @@ hipError_t launch_decode_split_scores(const SelectArgs& a, hipStream_t stream) {
 // The workspace that a call must bring depends on its rows' lengths alone: a call of few rows past the
 // tile kernel's candidates needs the row-wise path's, though the decode kernel leaves it unused.
 bool select_needs_scratch(int64_t rows, int32_t n_q, int64_t q_pos0, int32_t n_init, int32_t n_local, WinGrid grid) {
-  if (n_q > 1)
-    return !tile_grid(grid) || row_geom(q_pos0 + n_q - 1, n_init, n_local, 1 << 30).n_cand > kSelTileMaxCand;
+  if (n_q > 1) return row_geom(q_pos0 + n_q - 1, n_init, n_local, 1 << 30).n_cand > kSelTileMaxCand;
   const SelectPath path = select_path(rows, n_q, q_pos0, n_init, n_local, grid);
   return path == kPathRowwise || path == kPathDecodeSplit;
 }
@@ -339,7 +338,7 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
   const RowGeom gl = row_geom(pl, a.n_init, a.n_local, a.k_total);
   int32_t wf, wl;
   row_windows(gl, a.grid, pl, &wf, &wl);
-  if (gl.n_cand > 0 && wl >= wf && a.n_q >= kTileScoreMinRows && tile_grid(a.grid)) {
+  if (gl.n_cand > 0 && wl >= wf && a.n_q >= kTileScoreMinRows) {
     // many rows: 64-row units score on MFMA, each key fragment shared by the unit's rows
     hipError_t e = launch_block_scores(a, stream);
     return e != hipSuccess ? e : launch_topk<true, true>(a, stream);
