@@ -463,9 +463,14 @@ hipError_t launch_block_scores(const SelectArgs& a, hipStream_t stream) {
   const RowGeom g = row_geom(a.q_pos0 + a.n_q - 1, a.n_init, a.n_local, a.k_total);
   const int stages = (g.n_cand + (blocks ? 127 : 31)) / (blocks ? 128 : 32);
   b.n_wg = (a.n_q + 64 * kBsUnits - 1) / (64 * kBsUnits);
-  // chunks of candidates so that about four workgroups per CU are in flight, at least four stages each
-  int64_t chunks = (1024 + (int64_t)n_groups * b.n_wg - 1) / ((int64_t)n_groups * b.n_wg);
-  chunks = std::max<int64_t>(1, std::min<int64_t>(chunks, (stages + 3) / 4));
+  // Chunks of candidates so that about four workgroups per CU are in flight, at least four stages each; where
+  // those would not even be one per CU, shorter ones up to two per CU.  Measured with four and with at least
+  // one stage (us, 34 500 to 131 072 tokens): one key per block, 70 rows of 8 groups 18-24 and 9-10, 1000 of
+  // 8 25-30 and 16-20, 4096 of 8 23-51 and 25-55; (32, 16) grid 15-17 and 8-11, 22-30 and 21-39, 34-110 and
+  // 40-112.
+  const int64_t base = (int64_t)n_groups * b.n_wg;
+  int64_t chunks = std::max<int64_t>(1, std::min<int64_t>((1024 + base - 1) / base, (stages + 3) / 4));
+  if (base * chunks < 256) chunks = std::max(chunks, std::min<int64_t>(512 / base, stages));
   b.chunk_stages = (int)((stages + chunks - 1) / chunks);
   b.n_chunks = (stages + b.chunk_stages - 1) / b.chunk_stages;
   const dim3 grid((unsigned)((int64_t)n_groups * b.n_wg * b.n_chunks)), block(64 * kBsUnits);

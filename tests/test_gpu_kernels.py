@@ -279,6 +279,28 @@ def test_rowwise_select_edges(dev, C, n_q, k, n_init, n_local, grid, levels):
         say("  rows %d, tie swaps %d" % compare_selection(o, f16, kc16, n_q, q_pos0, sel, cnt, rows))
 
 
+# The same over calls whose block scores take chunks of one stage (32 or 128 candidates), of two and of four or
+# more: the fewer workgroups a call has, the shorter its chunks.
+@pytest.mark.parametrize("B,H,n_q,C,grid", [(1, 1, 16, 520, (64, 64)), (1, 8, 70, 1300, (64, 64)), (2, 8, 2048, 600, (64, 64)),
+                                            (2, 8, 1030, 515, (32, 16)), (1, 8, 600, 1100, (32, 16)), (1, 8, 1800, 640, (32, 16))])
+def test_rowwise_select_chunks(dev, B, H, n_q, C, grid):
+    say(f"row-wise select chunks B{B} H{H} n_q{n_q} C{C} grid {grid}")
+    k, T = 20, 64 * (C + 3) - 11
+    q_pos0, t_cap = T - n_q, -(-T // 64) * 64
+    nw = (T - grid[0]) // grid[1] + 1
+    s, o = shapes(B, H, 4, k, t_cap, nw, 1, 2, grid)
+    f = inputs.normal_bf16((B, H, n_q, 128), 15, 0, device=dev)
+    kc = inputs.normal_bf16((B, H, nw, 128), 15, 1, device=dev)
+    sel = torch.full((B, H, n_q, k), 777, dtype=torch.int16, device=dev)
+    cnt = torch.full((B, H, n_q), 777, dtype=torch.int16, device=dev)
+    ws = torch.empty(sp.sparda_workspace_size(s, sp.SPARDA_OP_FORECAST_SELECT, n_q, q_pos0), dtype=torch.uint8, device=dev)
+    sp.sparda_forecast_select(s, f, n_q, q_pos0, kc, sel, cnt, ws)
+    torch.cuda.synchronize()
+    rows = [(b, m, r) for b in range(B) for m in range(H) for r in sorted({0, n_q // 3, n_q - 1})]
+    say("  rows %d, tie swaps %d" % compare_selection(o, inputs.to_u16(f), inputs.to_u16(kc), n_q, q_pos0, sel.cpu().numpy(),
+                                                      cnt.cpu().numpy(), rows))
+
+
 # The multi-head selector's multi-row calls: the candidate counts at which the top-k takes more keys per lane (64, 128,
 # 256, 512, 1024, 2048) and the most it holds, both key grids (block scores read as they are, windows pooled).
 # `levels` draws the scores from so many values, so that ties decide and the sets must be the oracle's.
