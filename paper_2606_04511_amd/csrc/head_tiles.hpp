@@ -14,7 +14,8 @@
 // A workgroup's four wavefronts take up to four units (of the same group) over one chunk of keys,
 // staged 128 at a time in two LDS slots straight from memory (one barrier per 128 keys), so that a key
 // read from L2 serves up to 256 columns; with fewer units the wavefronts share a unit's keys.
-// Chunks fill the chip when there are few units: two launches,
+// Chunks fill the chip when there are few units: two launches (few units of few keys take one, at the end
+// of this file),
 //  * head_stats_kernel: per column and chunk the maximum and sum of 2^z over the keys the column's
 //    row sees (z = scale * log2 e * q . k), the first tile's maximum standing in for the running
 //    maximum (a reference only has to keep the exponent range, not the precision), one (reference, sum)
@@ -426,6 +427,204 @@ hipError_t launch_head_tiles(const HeadTileArgs& a, int G, hipStream_t stream) {
     case 8: return launch_head_tiles_g<8, kEmit>(a, stream);
     case 16: return launch_head_tiles_g<16, kEmit>(a, stream);
     default: return hipErrorInvalidValue;
+  }
+}
+
+// ---- few keys: one launch ---------------------------------------------------------------------
+//
+// A workgroup takes one unit and forms its products once: up to kHuKeys keys, 32 per tile, dealt to eight
+// wavefronts, which hold them (T tiles each) until the columns' maxima and sums have been exchanged
+// through LDS.  The keys are the A operand and the columns the B operand, so that a lane's accumulators are keys of one column (element e of
+// lane (n, h): key 8 (e / 4) + 4 h + e % 4 of the tile, column 32 nt + n) and the statistics need no
+// exchange between lanes but the two halves; the sum over a row's heads is one DPP step per doubling.
+//
+// What bounds it: latency (the rows, a wavefront's keys, two barriers, the stores), and from about one
+// workgroup per CU on the reads of the keys, which no two units share.  The two launches above
+// have both (and one launch whose four wavefronts formed every product twice was between them); us of
+// this kernel, the two launches, that one launch: 16 rows of one group, 4 heads, 124 keys 10, 14, 12; 64
+// rows of 2 groups against 249 keys 11.5, 24, 17 and against 499 15.4, 36, 26; 1000 rows of 8 groups,
+// one head, 499 keys 21, 55, 35.  The target's segments take it too: the whole training call on 300 tokens,
+// 100 rows of 2 groups, 4 heads 20.6, 43.3, 29.9.
+constexpr int kHuThreads = 512;
+constexpr int kHuWaves = kHuThreads / kWave;
+constexpr int kHuTileKeys = 32;
+constexpr int kHuMaxTiles = 4;  // per wavefront
+constexpr int kHuKeys = kHuTileKeys * kHuWaves * kHuMaxTiles;
+
+template <int G, int T, int kEmit>
+__global__ __launch_bounds__(kHuThreads) void head_unit_kernel(HeadTileArgs a) {
+  using namespace head_tiles;
+  constexpr int U = 64 / G;
+  __shared__ float red_m[kHuWaves][64], red_s[kHuWaves][64];
+  const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = blockIdx.x % a.n_groups;
+  const int unit = (int)(gridDim.x / a.n_groups) - 1 - (int)(blockIdx.x / a.n_groups);  // latest rows first
+  const int r0 = unit * U, nr = min(U, a.n_q - r0);
+  int32_t lo = 0;  // kWindows: the first window that the rows select from
+  if (kEmit == kWindows) {
+    const int64_t p_last = a.q_pos0 + r0 + nr - 1;
+    const RowGeom gl = row_geom(p_last, a.n_init, a.n_local, a.k_total);
+    if (gl.n_take >= gl.n_cand) return;  // then every row of the unit takes all its candidates
+    int32_t last;
+    row_windows(gl, a.grid, p_last, &lo, &last);
+  }
+  const int n_keys = last_key(a, r0 + nr - 1) + 1, vis0 = last_key(a, r0);
+
+  bf16x8 fb[2][8];
+  int vis[2];  // last key that the column's row sees
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) {
+    const int c = 32 * nt + n, row = min(c / G, nr - 1);
+    const uint16_t* src = a.q + (((int64_t)grp * G + c % G) * a.n_q + r0 + row) * kHeadDim + 32 * h;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) fb[nt][s] = as_bf16x8(ld16(src + 64 * (s >> 2) + 8 * (s & 3)));
+    vis[nt] = last_key(a, r0 + row);
+  }
+  const uint16_t* keys = a.keys + (int64_t)grp * a.key_cap * kHeadDim + 32 * h;
+  f32x16 z[T][2];  // products, then 2^(scaled product - maximum)
+  float m[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int k0 = kHuTileKeys * (wave + kHuWaves * t);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) z[t][0][e] = z[t][1][e] = 0.f;
+    const uint16_t* src = keys + (int64_t)min(k0 + n, n_keys - 1) * kHeadDim;
+    bf16x8 fa[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) fa[s] = as_bf16x8(ld16(src + 64 * (s >> 2) + 8 * (s & 3)));
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      z[t][0] = mfma32(fa[s], fb[0][s], z[t][0]);
+      z[t][1] = mfma32(fa[s], fb[1][s], z[t][1]);
+    }
+    if (k0 + kHuTileKeys - 1 > vis0) {  // keys that some row does not see
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (k0 + 8 * (e >> 2) + 4 * h + (e & 3) > vis[nt]) z[t][nt][e] = -INFINITY;
+    }
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) m[nt] = fmaxf(m[nt], z[t][nt][e]);
+  }
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) {
+    m[nt] = fmaxf(m[nt], __shfl_xor(m[nt], 32, kWave));
+    if (h == 0) red_m[wave][32 * nt + n] = m[nt];
+  }
+  __syncthreads();
+  float s[2] = {0.f, 0.f};
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) {
+#pragma unroll
+    for (int w = 0; w < kHuWaves; ++w) m[nt] = fmaxf(m[nt], red_m[w][32 * nt + n]);
+    const float ref = m[nt] > -INFINITY ? m[nt] * a.scale_log2 : 0.f;  // a row without a key: weights 0
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        z[t][nt][e] = __builtin_amdgcn_exp2f(fmaf(z[t][nt][e], a.scale_log2, -ref));
+        s[nt] += z[t][nt][e];
+      }
+    s[nt] += __shfl_xor(s[nt], 32, kWave);
+    if (h == 0) red_s[wave][32 * nt + n] = s[nt];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) {
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kHuWaves; ++w) sum += red_s[w][32 * nt + n];
+    const float inv = sum > 0.f ? 1.0f / sum : 0.f;
+    // each row's weights go to its first column's lane, which stores those that the row needs
+    const int row = 32 / G * nt + n / G;
+    int hi = -1;
+    if (n % G == 0 && row < nr) {
+      hi = n_keys - 1;
+      if (kEmit == kWindows) {
+        const int64_t p = a.q_pos0 + r0 + row;
+        const RowGeom g = row_geom(p, a.n_init, a.n_local, a.k_total);
+        int32_t first, wl;
+        row_windows(g, a.grid, p, &first, &wl);
+        hi = g.n_take < g.n_cand ? wl : -1;
+      }
+    }
+    float* out = a.out + ((int64_t)grp * a.n_q + r0 + min(row, nr - 1)) * a.out_stride - lo;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int k0 = kHuTileKeys * (wave + kHuWaves * t);
+#pragma unroll
+      for (int e0 = 0; e0 < 16; e0 += 8) {
+        float w[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          w[i] = z[t][nt][e0 + i] * inv;
+          if (G >= 2) w[i] += dpp_f<0xB1>(w[i]);    // lane ^ 1
+          if (G >= 4) w[i] += dpp_f<0x4E>(w[i]);    // lane ^ 2
+          if (G >= 8) w[i] += dpp_f<0x141>(w[i]);   // the other four of eight
+          if (G >= 16) w[i] += dpp_f<0x140>(w[i]);  // the other eight of sixteen
+        }
+        if (kEmit == kWindows) {
+#pragma unroll
+          for (int q = 0; q < 8; q += 4) {
+            const int key = k0 + 2 * (e0 + q) + 4 * h;
+            if (key >= lo && key + 3 <= hi) {
+              __builtin_memcpy(out + key, w + q, 4 * sizeof(float));  // one store, aligned to a float
+            } else {
+#pragma unroll
+              for (int i = 0; i < 4; ++i)
+                if (key + i >= lo && key + i <= hi) out[key + i] = w[q + i];
+            }
+          }
+        } else {  // the segment's keys 0-3 and 8-11 lie in lane half 0, 4-7 and 12-15 in half 1
+          float m15 = fmaxf(fmaxf(fmaxf(w[0], w[1]), fmaxf(w[2], w[3])), fmaxf(fmaxf(w[4], w[5]), w[6]));
+          float m16 = fmaxf(m15, w[7]);
+          if (h == 0) m15 = m16;
+          m15 = fmaxf(m15, __shfl_xor(m15, 32, kWave));
+          m16 = fmaxf(m16, __shfl_xor(m16, 32, kWave));
+          const int key = k0 + 2 * e0;
+          if (h == 0 && key <= hi) *reinterpret_cast<float2*>(out + 2 * (key >> 4)) = make_float2(m15, m16);
+        }
+      }
+    }
+  }
+}
+
+template <int G, int kEmit>
+hipError_t launch_head_units_g(const HeadTileArgs& a, int n_keys, hipStream_t stream) {
+  const dim3 grid((unsigned)((int64_t)a.n_groups * ((a.n_q + 64 / G - 1) / (64 / G)))), block(kHuThreads);
+  constexpr int kRound = kHuTileKeys * kHuWaves;
+  if (n_keys <= kRound)
+    hipLaunchKernelGGL((head_unit_kernel<G, 1, kEmit>), grid, block, 0, stream, a);
+  else if (n_keys <= 2 * kRound)
+    hipLaunchKernelGGL((head_unit_kernel<G, 2, kEmit>), grid, block, 0, stream, a);
+  else
+    hipLaunchKernelGGL((head_unit_kernel<G, kHuMaxTiles, kEmit>), grid, block, 0, stream, a);
+  return hipGetLastError();
+}
+
+// Where one launch of units is the faster: while the units that have to select fill the chip at most once
+// (a wavefront's four tiles: one workgroup per CU) or twice (two tiles).  Measured, one launch against two
+// (us), for 128, 504, 940 and 2000 such units: 499 keys 21 / 55, 33 / 43, -, 119 / 57; 124 to 249 keys
+// 13 / 34, 21 / 28, 37 / 27, 54 / 38; 1017 keys 32 / 57, 51 / 45, -, 199 / 105.
+inline bool head_units_fit(const HeadTileArgs& a, int G, int n_keys) {
+  const int U = 64 / G;
+  const int64_t first = (int64_t)a.k_total * kBlock - a.q_pos0;  // rows before it take every candidate
+  const int64_t units = (a.n_q + U - 1) / U - (first > 0 ? first / U : 0);
+  return n_keys <= kHuKeys && units * a.n_groups <= (n_keys <= kHuKeys / 2 ? 512 : 256);
+}
+
+template <int kEmit>
+hipError_t launch_head_units(const HeadTileArgs& a, int G, int n_keys, hipStream_t stream) {
+  switch (G) {
+    case 1: return launch_head_units_g<1, kEmit>(a, n_keys, stream);
+    case 2: return launch_head_units_g<2, kEmit>(a, n_keys, stream);
+    case 4: return launch_head_units_g<4, kEmit>(a, n_keys, stream);
+    case 8: return launch_head_units_g<8, kEmit>(a, n_keys, stream);
+    default: return launch_head_units_g<16, kEmit>(a, n_keys, stream);
   }
 }
 

@@ -16,11 +16,13 @@
 // Kernels:
 //   pair_compress_kernel -- the (2, 1) windows of the raw keys into the workspace: float64 sum of
 //                           the pair, one rounding to bf16 (as every compressed key).
-//   head_stats_kernel, head_weights_kernel (head_tiles.hpp) -- for G in {1, 2, 4, 8, 16}: the
-//                           target's shared weights for 64 / G rows at a time (64 (row, head) columns
-//                           on 32x32x16 MFMA), max-pooled to segments of 16 fine windows in the
-//                           workspace (2 floats per segment instead of one per fine window).
-//   kl_predict_kernel    -- for the same G: F . K~p of 64 rows at a time on MFMA into the workspace.
+//   head_stats_kernel, head_weights_kernel, or head_unit_kernel for few fine windows and units
+//                           (head_tiles.hpp) -- for G in {1, 2, 4, 8, 16}: the target's shared weights
+//                           for 64 / G rows at a time (64 (row, head) columns on 32x32x16 MFMA),
+//                           max-pooled to segments of 16 fine windows in the workspace (2 floats per
+//                           segment instead of one per fine window).
+//   kl_predict_kernel    -- for the same G, beside the two launches: F . K~p of 64 rows at a time on
+//                           MFMA into the workspace.
 //   kl_row_kernel        -- one 512-thread workgroup per query row.  Target: the max-pool of those
 //                           weights into the positions, or for other G 16-window x 16-head
 //                           MFMA tiles (A = the windows, B = the group's query rows padded to 16
@@ -154,9 +156,10 @@ __global__ __launch_bounds__(kHtThreads, 2) void kl_predict_kernel(HeadTileArgs 
   });
 }
 
-// kPre: the segment maxima of the target's shared weights are in a.sw (head_weights_kernel); the row
+// kLogits: the row's logits are in a.z (kl_predict_kernel); otherwise it computes them itself.
+// kPre: the segment maxima of the target's shared weights are in a.sw (head_tiles.hpp); the row
 // max-pools them into its positions.  Otherwise the row computes them itself (16-window x 16-column MFMA tiles).
-template <bool kPre>
+template <bool kPre, bool kLogits>
 __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
   // Per-position arrays, sized by the host for the call's largest row (kl_lds_layout): the pooled
   // target (float bits for the atomic max), the predicted distribution, the top-k list and the
@@ -188,15 +191,17 @@ __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
     // within [w s, w s + l), i.e. i in [w s, w s + l - 2]: l / 16 segments of 16 fine windows, the last
     // one without its last window; every position complete at p has them
     const float2* seg = reinterpret_cast<const float2*>(a.sw + row * a.sw_stride);
-    const float* z = a.z + row * a.sw_stride;  // the row's logits, from kl_predict_kernel
+    const float* z = kLogits ? a.z + row * a.sw_stride : nullptr;  // the row's logits, from kl_predict_kernel
     const int gs = a.grid.s / 16, gl = a.grid.l / 16;
     for (int w = tid; w < N; w += kDecThreads) {
-      const float zw = z[w];
       float m = seg[w * gs + gl - 1].x;
       for (int i = 0; i < gl - 1; ++i) m = fmaxf(m, seg[w * gs + i].y);
       Tp[w] = m;
-      Pp[w] = zw;
-      zl = fmaxf(zl, zw);
+      if (kLogits) {
+        const float zw = z[w];
+        Pp[w] = zw;
+        zl = fmaxf(zl, zw);
+      }
       chosen[w] = 0;
     }
   } else {  // MFMA tiles of 16 fine windows x the group's heads
@@ -277,7 +282,7 @@ __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
   // ---- prediction: the logits, from kl_predict_kernel (above) or a Forecast GEMV over the positions (16
   // lanes per position), then their softmax.  A position's entries are read and written by its own
   // thread from here to the top-k, and between the top-k and the gradient.
-  if (!kPre) {
+  if (!kLogits) {
     const int c = lane & 15, rs = lane >> 4;
     float fv[8];
     {
@@ -303,7 +308,7 @@ __global__ __launch_bounds__(kDecThreads) void kl_row_kernel(KlArgs a) {
       if (c == 0 && w < N) Pp[w] = d;
     }
   }
-  if (!kPre) {
+  if (!kLogits) {
     __syncthreads();
     for (int w = tid; w < N; w += kDecThreads) zl = fmaxf(zl, Pp[w]);
   }
@@ -474,8 +479,16 @@ hipError_t launch_indexer_kl(const uint16_t* q, const uint16_t* k, const uint16_
     t.n_q = n_q;
     t.grid = WinGrid{2, 1};
     t.scale_log2 = a.scale_log2;
+    hipError_t e;
+    if (head_units_fit(t, G, (int)nt)) {  // at most 63 positions, whose logits a row forms itself
+      e = launch_head_units<head_tiles::kSegments>(t, G, (int)nt, stream);
+      if (e != hipSuccess) return e;
+      a.z = nullptr;
+      hipLaunchKernelGGL((kl_row_kernel<true, false>), dim3((unsigned)(rows_g * n_q)), dim3(kDecThreads), lds, stream, a);
+      return hipGetLastError();
+    }
     plan_head_tiles(t, G, kHeadDim / (2 * G));
-    hipError_t e = launch_head_tiles<head_tiles::kSegments>(t, G, stream);
+    e = launch_head_tiles<head_tiles::kSegments>(t, G, stream);
     if (e != hipSuccess) return e;
     // the logits of a row's positions after its segment maxima: of the fine windows' nt floats per row
     // the maxima take 2 per 16 and the logits 1 per 16 or 64
@@ -496,9 +509,9 @@ hipError_t launch_indexer_kl(const uint16_t* q, const uint16_t* k, const uint16_
                        0, stream, z);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kl_row_kernel<true>, dim3((unsigned)(rows_g * n_q)), dim3(kDecThreads), lds, stream, a);
+    hipLaunchKernelGGL((kl_row_kernel<true, true>), dim3((unsigned)(rows_g * n_q)), dim3(kDecThreads), lds, stream, a);
   } else {
-    hipLaunchKernelGGL(kl_row_kernel<false>, dim3((unsigned)(rows_g * n_q)), dim3(kDecThreads), lds, stream, a);
+    hipLaunchKernelGGL((kl_row_kernel<false, false>), dim3((unsigned)(rows_g * n_q)), dim3(kDecThreads), lds, stream, a);
   }
   return hipGetLastError();
 }

@@ -209,7 +209,11 @@ def test_attention_unwritten_tail(dev, G, n_q, T):
 # (float32 products and sums), at most 2^-24 * 128 * 170 = 1.3e-3 in log2 units, so weights and losses
 # are off by less than 1e-3 relatively; the others keep float32's 1e-5.
 @pytest.mark.parametrize("G,n_q,T,hot", [(1, 40, 900, 1.0), (1, 130, 2500, 16.0), (2, 90, 1200, 16.0), (4, 16, 700, 16.0),
-                                         (4, 17, 6000, 1.0), (16, 5, 5000, 16.0), (16, 3, 64, 1.0)])
+                                         (4, 17, 6000, 1.0), (16, 5, 5000, 16.0), (16, 3, 64, 1.0),
+                                         # one launch: the tiles a wavefront holds (256, 512, 1024 fine windows) and
+                                         # the first T past them, one position, more units than it takes
+                                         (1, 70, 257, 1.0), (2, 33, 258, 16.0), (4, 20, 513, 1.0), (8, 9, 514, 16.0),
+                                         (16, 7, 1025, 1.0), (4, 16, 1026, 16.0), (4, 2, 34, 1.0), (16, 700, 740, 1.0)])
 def test_indexer_kl_target_chunks(dev, G, n_q, T, hot):
     say(f"indexer target G{G} n_q{n_q} T{T} hot {hot}")
     H, q_pos0, t_cap, k_top = 2, T - n_q, -(-T // 64) * 64, 8
