@@ -175,7 +175,8 @@ int sparda_forecast_score_max(const sparda_shape* shape, const void* f, int32_t 
  *   ws, ws_bytes: device workspace of at least sparda_workspace_size(SPARDA_OP_MULTIHEAD_SELECT)
  *                (0 bytes for decode with G in {1, 2, 4, 8} up to about 38K windows times G).
  * Per row: for every head h of the group, z_hi = sm_scale q_h . K~_i over the complete windows i,
- * a_hi = softmax_i(z_hi) (float32, exp2 domain, each head's exact maximum subtracted); window i's
+ * a_hi = softmax_i(z_hi) (float32, exp2 domain, each head's exact maximum subtracted, or in larger
+ * multi-row calls a reference at most 2^60 below it); window i's
  * shared score is sum_h a_hi; candidate j scores the largest shared score of the windows that
  * overlap block j and are complete at p; forced blocks, ordering and ties as for
  * sparda_forecast_select.

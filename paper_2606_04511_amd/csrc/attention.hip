@@ -607,7 +607,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(AttnArgs 
     A1 *= keep;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      if (pm[i] == -INFINITY) continue;  // a split without a token: its accumulators are not written
+      if (pm[i] == -INFINITY) continue;  // a split without a token weighs nothing
       const float w = __builtin_amdgcn_exp2f(pm[i] - mx);
       L = fmaf(pl[i], w, L);
       A0 = fmaf(pa[i].x, w, A0);

@@ -200,6 +200,12 @@ def test_attention_unwritten_tail(dev, G, n_q, T):
         sp.sparda_decode_step(s, fd, q_pos0, cd, qd, kd, vd, SCALE, sel2, cnt2, out2, w)
         torch.cuda.synchronize()
         assert torch.equal(sel2, sel) and torch.equal(cnt2, cnt) and torch.equal(out2.view(torch.int16), out.view(torch.int16))
+        idx = sel.long().clamp_min(0)[..., 0, :, None, None]  # staged copies of the same blocks
+        stage = [x.view(B, H, -1, 64, 128).gather(2, idx.expand(B, H, k, 64, 128)).contiguous() for x in (kd, vd)]
+        out3 = torch.full_like(out, math.nan)
+        sp.sparda_sparse_attn(s, qd, 1, q_pos0, stage[0], stage[1], 1, sel, cnt, SCALE, out3, ws[1])
+        torch.cuda.synchronize()
+        assert torch.equal(out3.view(torch.int16), out.view(torch.int16))
 
 
 # The indexer-training target over chunks of keys: 1, 2 to 3 and 5 or more units of 64 / G rows (the
