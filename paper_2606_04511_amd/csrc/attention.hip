@@ -327,10 +327,10 @@ __global__ __launch_bounds__(NW * 64) void decode_step_kernel(SelectArgs s, Attn
 // Lane (n, g) accumulates dims 16 dt + 4 g + e of head n in o[dt]; the wavefronts' states merge
 // through LDS (the buffers' space) as in sparse_attn_kernel.
 //
-// What bounds it: the memory stream and what frames it (selection, first loads, merge).  The step of the
-// paper's layout at 128K, batch 32 (201 MB of K and V, 64 rows, four splits): 46.6 us; with K and V
-// through registers, V gathered from LDS two bytes at a time and library exp2 and rounding 51.7 us.  80
-// rows of 7 heads, 48 blocks each: 29.6 us, 35.6 before.
+// What bounds it: the memory stream and what frames it (selection, first loads, merge).  The fused step's
+// kernel in the paper's layout at 128K, batch 32 (201 MB of K and V, 64 rows, four splits): 43.5 us; with
+// K and V through registers, V gathered from LDS two bytes at a time and library exp2 and rounding 51.7
+// us.  80 rows of 7 heads, 48 blocks each: 29.8 us, 35.6 before.
 constexpr int kWideHalf = 32;                                // tokens per half block
 constexpr int kWideBuf = kWideHalf * kHeadDim * 2;           // bytes of a half's K or V
 

@@ -29,9 +29,10 @@
 // 16-cycle MFMA, the third costs 8 cycles), and a block ends with its busiest wavefront (1.28 to
 // 1.5 times the mean).  Reading every block from a 256 KiB footprint instead changes 4 %, so memory is
 // not the limit.  A 32K prefill of 32 / 8 heads, k = 64, neighbouring rows sharing 0.8 of their
-// Forecast variance: 3.95 ms, 519 TFLOP/s of attended pairs (5.93 ms with K and V staged through
-// registers, V transposed on the way, and a branch around every product; 3.88 with the denominators
-// summed by two MFMAs of the rounded P against ones, which holds fewer bits of them).  Tried and slower: eight wavefronts with a ring of four blocks
+// Forecast variance: 3.87 ms, 529 TFLOP/s of attended pairs (5.91 ms with K and V staged through
+// registers, V transposed on the way, and a branch around every product; 1.5 % less with the denominators
+// summed by two MFMAs of the rounded P against ones, which holds fewer bits of them); the last 8192 rows
+// of 32 / 2 heads, k = 96: 1.24 ms (1.97).  Tried and slower: eight wavefronts with a ring of four blocks
 // and one barrier per block (4.70 ms); one wavefront bringing the blocks for 7, 11 or 15 others without
 // barriers (4.0 ms; the ring is too short to even out the wavefronts; 1.12 ms at 16 heads per group);
 // one N-tile per wavefront on 16 wavefronts (4.33 ms).
