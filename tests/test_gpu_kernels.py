@@ -208,8 +208,9 @@ def test_attention_unwritten_tail(dev, G, n_q, T):
         assert torch.equal(out3.view(torch.int16), out.view(torch.int16))
 
 
-# The indexer-training target over chunks of keys: 1, 2 to 3 and 5 or more units of 64 / G rows (the
-# wavefronts of a workgroup share a unit's keys below 4), one and several chunks, and keys late in the
+# The indexer-training target, in one launch (up to 1024 fine windows) and over chunks of keys: 1, 2 to 3 and 5
+# or more units of 64 / G rows (the wavefronts of a workgroup share a unit's keys below 4), one and several
+# chunks, and keys late in the
 # context whose logits lie up to 2^100 above the first tile's (the sums are formed again from the
 # true maxima).  With those, a logit z carries an absolute error of up to 128 ulps of sum |q_d k_d|
 # (float32 products and sums), at most 2^-24 * 128 * 170 = 1.3e-3 in log2 units, so weights and losses
@@ -219,7 +220,9 @@ def test_attention_unwritten_tail(dev, G, n_q, T):
                                          # one launch: the tiles a wavefront holds (256, 512, 1024 fine windows) and
                                          # the first T past them, one position, more units than it takes
                                          (1, 70, 257, 1.0), (2, 33, 258, 16.0), (4, 20, 513, 1.0), (8, 9, 514, 16.0),
-                                         (16, 7, 1025, 1.0), (4, 16, 1026, 16.0), (4, 2, 34, 1.0), (16, 700, 740, 1.0)])
+                                         (16, 7, 1025, 1.0), (4, 16, 1026, 16.0), (4, 2, 34, 1.0), (16, 700, 740, 1.0),
+                                         # two launches with one unit
+                                         (4, 9, 1500, 16.0), (16, 3, 2000, 1.0)])
 def test_indexer_kl_target_chunks(dev, G, n_q, T, hot):
     say(f"indexer target G{G} n_q{n_q} T{T} hot {hot}")
     H, q_pos0, t_cap, k_top = 2, T - n_q, -(-T // 64) * 64, 8
