@@ -434,9 +434,10 @@ hipError_t launch_head_tiles(const HeadTileArgs& a, int G, hipStream_t stream) {
 //
 // A workgroup takes one unit and forms its products once: up to kHuKeys keys, 32 per tile, dealt to eight
 // wavefronts, which hold them (T tiles each) until the columns' maxima and sums have been exchanged
-// through LDS.  The keys are the A operand and the columns the B operand, so that a lane's accumulators are keys of one column (element e of
-// lane (n, h): key 8 (e / 4) + 4 h + e % 4 of the tile, column 32 nt + n) and the statistics need no
-// exchange between lanes but the two halves; the sum over a row's heads is one DPP step per doubling.
+// through LDS.  The keys are the A operand and the columns the B operand, so that a lane's accumulators
+// are keys of one column (element e of lane (n, h): key 8 (e / 4) + 4 h + e % 4 of the tile, column 32 nt +
+// n) and the statistics need no exchange between lanes but the two halves; the sum over a row's heads is
+// one DPP step per doubling.  Every unit that selects, and every training row, sees a key.
 //
 // What bounds it: latency (the rows, a wavefront's keys, two barriers, the stores), and from about one
 // workgroup per CU on the reads of the keys, which no two units share.  The two launches above
